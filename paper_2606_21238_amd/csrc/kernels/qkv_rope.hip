@@ -6,25 +6,19 @@
 //   q, k = rotary(y_q, y_k) at each token's absolute position; v = y_v
 //
 // One kernel does the projection and the rotation, so y never goes to memory:
-//  * a work-group computes a 256-token x 256-output tile of y with v_mfma_f32_32x32x16_bf16;
-//    its 8 waves form two groups of 4 (waves w and w + 4 share a SIMD), group g owning tokens
-//    128 g .. +127 and each wave 64 tokens x 128 outputs (2 x 4 accumulator blocks of 32 x 32);
-//  * x and W tiles of 32 columns of H stream global -> LDS with 16-byte direct loads (SGPR
-//    base + 32-bit lane offsets) into a 4-stage ring, three stages ahead; a row's 16-byte
-//    chunk c is stored at c ^ ((row / 4) % 4), so 16 lanes of an operand read hit 16
-//    different 16-byte slots of the banks;
-//  * the two groups run half a step apart (ping-pong): while one group's waves issue their
-//    16 MFMAs of a step, the other group's waves, on the same SIMDs, read their operands of
-//    the step from LDS and issue their share of the loads; every half step ends at a
-//    work-group barrier, so the SIMDs' matrix units are fed by one wave or the other;
-//  * the epilogue rounds y to bf16 into LDS as a [token][output] tile, then every thread
-//    takes 16-byte chunks of a token's head: it rotates the (i, i + D/2) pairs in fp32 with the
-//    token's (cos, sin) (its own chunk and the partner chunk D/2 away), rounds again and
-//    stores the chunk whole into Q, K or V.  Values pass through.
-// The (cos, sin) table of every token (D/2 angles p * theta^(-2i/D), in fp64 reduced mod 2 pi,
-// then fp32 sine and cosine) comes from a small pre-pass into the caller's workspace; it finds
-// each token's position from cu_q / seq_lens (suffix token i of request r sits at
-// L_r - S_r + i).
+//  * qkv_gemm_rope_kernel (prefill batches): 256- or 128-token x 256-output tiles, 4 waves, one
+//    per SIMD, rotation in registers;
+//  * qkv_ksplit_kernel (decode steps, short questions): 32- or 64-token x 32- or 64-output tiles
+//    whose waves split H.
+// Both use v_mfma_f32_32x32x16_bf16 and stream x and W global -> LDS with 16-byte direct loads
+// (SGPR base + 32-bit lane offsets) in stages of 64 columns of H, so that every load instruction
+// takes whole 128-byte lines of 8 rows (stages of 32 columns, half lines, measured 53 us against
+// 41 for 16 tokens x 8192 x 10240, where W comes from HBM).  A row's 16-byte chunk c is stored at
+// c ^ ((row / 2) % 8), so 16 lanes of an operand read hit 16 different 16-byte slots of the banks.
+// The (cos, sin) pairs of a token (D/2 angles p * theta^(-2i/D), in fp64 reduced mod 2 pi, then
+// fp32 sine and cosine) come from a small pre-pass into the caller's workspace for the first
+// kernel; the second computes its tile's own.  A token's position is found from cu_q / seq_lens
+// (suffix token i of request r sits at L_r - S_r + i).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,23 +30,23 @@
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int kTM = 256;        // tokens per work-group tile
-constexpr int kTN = 256;        // outputs per work-group tile
-constexpr int kKB = 32;         // columns of H per ring stage
-constexpr int kStages = 4;
-constexpr int kThreads = 512;
-constexpr int kGroupM = 4;       // token tiles per group of the tile order
-constexpr int kStageBytes = (kTM + kTN) * kKB * 2;       // x tile then W tile: 32 KiB
-constexpr int kLoadsX = kTM * kKB * 2 / (kThreads * 16);  // 16-byte loads per thread per x tile
-constexpr int kLoadsW = kTN * kKB * 2 / (kThreads * 16);
-static_assert(kLoadsX == 2 && kLoadsW == 2, "two loads of each tile per thread");
+constexpr int kTN = 256;        // outputs per work-group tile of the prefill kernel
+constexpr int kKC = 64;         // columns of H per stage (the last stage may hold 32)
+constexpr int kGroupTokens = 1024;   // tokens per group of the tile order
 
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {  // nearest even; inputs finite
   const uint32_t u = __builtin_bit_cast(uint32_t, f);
   return static_cast<uint16_t>((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {  // nearest even, one instruction
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __builtin_bit_cast(float, static_cast<uint32_t>(b) << 16);
@@ -66,6 +60,12 @@ __device__ __forceinline__ void load_lds16(const void* base, uint32_t ofs, lds_v
   const uint32_t m = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(l));
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(ofs), "s"(base), "s"(m)
                : "memory", "m0");
+}
+
+// 4 bytes per lane from global memory (a 64-bit address per lane) into LDS bytes [M0 + 4 l, + 4).
+__device__ __forceinline__ void load_lds4(const void* g, lds_void* l) {
+  const uint32_t m = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(l));
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(m) : "memory", "m0");
 }
 
 // (cos, sin) of every token's D/2 rotary angles: tab[t][i], i < D/2.  A work-group computes
@@ -101,155 +101,36 @@ __global__ __launch_bounds__(256) void rope_table_kernel(int64_t n_tokens, const
   }
 }
 
+// Stores a finished TM x TN tile of y (bf16 in LDS at ep, [token][output], rows `pitch` bytes
+// apart): every thread takes 16-byte chunks of a token's head and stores them whole.  ROT: the
+// tile is not rotated yet; query and key chunks are rotated here against the chunk `partner`
+// local columns away.  col(o): the output (head * D + dim) of local column o (chunks of 8 are
+// consecutive outputs); cs_of(row, i): the (cos, sin) pairs of dims i .. i + 7 of tile row `row`.
 // POOL: K and V go straight into the paged pools (layout V1; k_out and v_out are then the
-// pools) at slots[t] instead of into [token][head][dim] rows: K rows as 16-byte chunks, V (dim-major blocks) as 8 consecutive tokens of one dim per
+// pools) at the tile's slots (tslot, -1 past the last token) instead of into [token][head][dim]
+// rows: K rows as 16-byte chunks, V (dim-major blocks) as 8 consecutive tokens of one dim per
 // 16-byte store where the 8 tokens hold 8 aligned consecutive slots, else one 2-byte store per
 // token.  Slots outside [0, n_slots) are skipped, as the scatter does.
-template <int D, bool POOL>
-__global__ __launch_bounds__(kThreads, 1) void qkv_gemm_rope_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, int n_tokens, int hidden,
-    int n_out, int hq, int hkv, const float2* __restrict__ tab, uint16_t* __restrict__ q_out,
-    uint16_t* __restrict__ k_out, uint16_t* __restrict__ v_out, const int32_t* __restrict__ slots,
-    int64_t n_slots) {
-  __shared__ __attribute__((aligned(1024))) char smem[kTM * (kTN * 2 + 16)];   // ring, then the y tile
-  __shared__ int32_t tslot[POOL ? kTM : 1];                                      // the tile's slots
-  // Tile order.  Work-groups are dealt to the 8 XCDs in turn (b -> XCD b % 8) and each XCD has
-  // its own L2, so logical tile L = (b % 8) * (G / 8) + b / 8 gives every XCD a contiguous run
-  // of tiles; runs go over groups of kGroupM token tiles output-tile by output-tile, so the
-  // ~32 tiles one XCD holds at a time share 4 x tiles and 8 W tiles in its L2.
-  const int n_tiles_n = n_out / kTN + (n_out % kTN ? 1 : 0);
-  const int n_tiles_m = n_tokens / kTM + (n_tokens % kTM ? 1 : 0);
-  const int b = blockIdx.x, full = gridDim.x & ~7;
-  const int L = b < full ? (b % 8) * (full / 8) + b / 8 : b;
-  const int group = L / (kGroupM * n_tiles_n), in_group = L % (kGroupM * n_tiles_n);
-  const int first_m = group * kGroupM, gm = min(n_tiles_m - first_m, kGroupM);
-  const int tile_m = first_m + in_group % gm, tile_n = in_group / gm;
-  const int t0 = tile_m * kTM, n0 = tile_n * kTN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = wave >> 2, wi = wave & 3;
-  const int l32 = lane & 31, hg = lane >> 5;
-  const int row0 = grp * 128 + (wi & 1) * 64;      // wave's 64 tokens of the tile
-  const int col0 = (wi >> 1) * 128;                // wave's 128 outputs of the tile
-
-  uint32_t xofs[kLoadsX], wofs[kLoadsW];          // byte offsets from the tile's first row
-#pragma unroll
-  for (int i = 0; i < kLoadsX; ++i) {
-    const int row = 128 * i + 16 * wave + lane / 4;
-    const int c = (lane % 4) ^ ((row >> 2) & 3);
-    const int t = min(t0 + row, n_tokens - 1) - t0;
-    xofs[i] = static_cast<uint32_t>(t * hidden + c * 8) * 2u;
-    const int n = min(n0 + row, n_out - 1) - n0;
-    wofs[i] = static_cast<uint32_t>(n * hidden + c * 8) * 2u;
-  }
-  const uint16_t* xbase = x + static_cast<int64_t>(t0) * hidden;
-  const uint16_t* wbase = w + static_cast<int64_t>(n0) * hidden;
-  const int n_k = hidden / kKB;
-  auto issue = [&](int s) {       // stages past the end reload the last one into a free buffer
-    char* st = smem + (s % kStages) * kStageBytes;
-    const int k0 = min(s, n_k - 1) * kKB;
-#pragma unroll
-    for (int i = 0; i < kLoadsX; ++i)
-      load_lds16(xbase + k0, xofs[i], (lds_void*)(st + i * 8192 + wave * 1024));
-#pragma unroll
-    for (int i = 0; i < kLoadsW; ++i)
-      load_lds16(wbase + k0, wofs[i], (lds_void*)(st + kTM * kKB * 2 + i * 8192 + wave * 1024));
-  };
-
-  f32x16_t acc[2][4];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x16_t{};
-
-  const int xr0 = row0 + l32, wr0 = col0 + l32;
-  bf16x8_t a[2][2], bq[2][4];
-  auto read_frags = [&](int s) {
-    const char* xb = smem + (s % kStages) * kStageBytes;
-    const char* wb = xb + kTM * kKB * 2;
-#pragma unroll
-    for (int ks = 0; ks < kKB / 16; ++ks) {
-      const int c = ks * 2 + hg;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        const int r = xr0 + mb * 32;
-        a[ks][mb] = *reinterpret_cast<const bf16x8_t*>(xb + r * 64 + ((c ^ ((r >> 2) & 3)) * 16));
-      }
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        const int r = wr0 + nb * 32;
-        bq[ks][nb] = *reinterpret_cast<const bf16x8_t*>(wb + r * 64 + ((c ^ ((r >> 2) & 3)) * 16));
-      }
-    }
-  };
-  auto mfmas = [&]() {
-#pragma unroll
-    for (int ks = 0; ks < kKB / 16; ++ks)
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][mb], bq[ks][nb], acc[mb][nb], 0, 0, 0);
-  };
-
-  // ---- main loop, in half steps that all end at a work-group barrier.  Group 0 reads step s
-  // in half step 2s and multiplies in 2s + 1; group 1 reads in 2s + 1 and multiplies in 2s + 2.
-  // A wave issues its share of stage s + 3 right after reading step s; that stage's buffer held
-  // stage s - 1, which group 0 read in half step 2s - 2 and group 1 in 2s - 1, both done.  Each
-  // wave has 4 loads per stage; vmcnt(8) at the end of a half step leaves at most its two
-  // newest stages in flight, so stage s + 1 is in LDS (barrier) before group 0 reads it in
-  // half step 2s + 2.  Stages past the end are issued as well (a copy of the last one into a
-  // buffer nobody reads any more), which keeps the counts constant.
-  for (int s = 0; s < kStages - 1; ++s) issue(s);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (kLoadsX + kLoadsW)) : "memory");
-  if (grp == 1) asm volatile("s_barrier" ::: "memory");       // group 1 runs one half step behind
-  for (int s = 0; s < n_k; ++s) {
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(s);
-    issue(s + kStages - 1);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (kLoadsX + kLoadsW)) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (kLoadsX + kLoadsW)) : "memory");
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  if (grp == 0) asm volatile("s_barrier" ::: "memory");       // same barrier count in both groups
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // no LDS write may still be in flight
-
-  // ---- epilogue: y tile (bf16) -> LDS [token][output] (row pitch kPitch bytes), then each
-  // thread rotates 16-byte chunks with their partner chunk D/2 away and stores them whole
-  asm volatile("s_barrier" ::: "memory");
-  constexpr int kPitch = kTN * 2 + 16;
-  char* ep = smem;
-  if constexpr (POOL)   // read once here (published by the barrier below), not per chunk
-    if (tid < kTM) tslot[tid] = t0 + tid < n_tokens ? slots[t0 + tid] : -1;
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = row0 + mb * 32 + (r / 4) * 8 + hg * 4 + (r % 4);
-        *reinterpret_cast<uint16_t*>(ep + row * kPitch + (col0 + nb * 32 + l32) * 2) = f32_to_bf16(acc[mb][nb][r]);
-      }
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+template <int D, bool POOL, bool ROT, int TM, int TN, int THREADS, class Col, class Cs>
+__device__ __forceinline__ void store_tile(const char* ep, int pitch, int t0, int n_tokens, Col col, int n_out,
+                                           int partner, Cs cs_of, const int32_t* tslot, int hq, int hkv,
+                                           uint16_t* __restrict__ q_out, uint16_t* __restrict__ k_out,
+                                           uint16_t* __restrict__ v_out, int64_t n_slots) {
+  const int tid = threadIdx.x;
   const int nrot = (hq + hkv) * D;
-  typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 #pragma unroll 4
-  for (int it = 0; it < kTM * kTN / 8 / kThreads; ++it) {
-    const int qc = it * kThreads + tid;
-    const int row = qc / (kTN / 8), o = (qc % (kTN / 8)) * 8;
-    const int t = t0 + row, n = n0 + o;
+  for (int qc = tid; qc < TM * TN / 8; qc += THREADS) {
+    const int row = qc / (TN / 8), o = (qc % (TN / 8)) * 8;
+    const int t = t0 + row, n = col(o);
     if (t >= n_tokens || n >= n_out) continue;
     if (POOL && n >= nrot) continue;               // V: the pass below
     const int head = n / D, i0 = n % D;
-    const u32x4_t own = *reinterpret_cast<const u32x4_t*>(ep + row * kPitch + o * 2);
+    const u32x4_t own = *reinterpret_cast<const u32x4_t*>(ep + row * pitch + o * 2);
     u32x4_t res = own;
-    if (n < nrot) {
+    if (ROT && n < nrot) {
       const bool lo = i0 < D / 2;
-      const u32x4_t par = *reinterpret_cast<const u32x4_t*>(ep + row * kPitch + (lo ? o + D / 2 : o - D / 2) * 2);
-      const float4* cs = reinterpret_cast<const float4*>(tab + static_cast<int64_t>(t) * (D / 2) + (lo ? i0 : i0 - D / 2));
+      const u32x4_t par = *reinterpret_cast<const u32x4_t*>(ep + row * pitch + (lo ? o + partner : o - partner) * 2);
+      const float4* cs = cs_of(row, lo ? i0 : i0 - D / 2);
       const float sg = lo ? -1.f : 1.f;      // lo: a c - b s; hi: a c + b s (a own, b partner)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -280,12 +161,11 @@ __global__ __launch_bounds__(kThreads, 1) void qkv_gemm_rope_kernel(
   if constexpr (POOL) {
     // V columns of the tile into the dim-major pool: item p is 8 tokens (rows 8 g .. 8 g + 7)
     // of one output column; consecutive threads take consecutive columns of the same tokens.
-    if (n0 + kTN > nrot) {                                        // uniform
+    if (col(TN - 1) >= nrot) {                                    // uniform
 #pragma unroll 2
-      for (int it = 0; it < (kTM / 8) * kTN / kThreads; ++it) {
-        const int p = it * kThreads + tid;
-        const int g = p / kTN, oc = p % kTN;
-        const int n = n0 + oc, tf = t0 + 8 * g;
+      for (int p = tid; p < (TM / 8) * TN; p += THREADS) {
+        const int g = p / TN, oc = p % TN;
+        const int n = col(oc), tf = t0 + 8 * g;
         if (n < nrot || n >= n_out || tf >= n_tokens) continue;
         const int vh = (n - nrot) / D, dim = (n - nrot) % D;
         int32_t sl[8];
@@ -293,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 1) void qkv_gemm_rope_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           sl[j] = tslot[8 * g + j];                               // -1 past the last token
-          val[j] = *reinterpret_cast<const uint16_t*>(ep + (8 * g + j) * kPitch + oc * 2);
+          val[j] = *reinterpret_cast<const uint16_t*>(ep + (8 * g + j) * pitch + oc * 2);
         }
         bool run = (sl[0] & 7) == 0 && sl[0] >= 0 && sl[0] + 7 < n_slots;
 #pragma unroll
@@ -315,9 +195,430 @@ __global__ __launch_bounds__(kThreads, 1) void qkv_gemm_rope_kernel(
   }
 }
 
+// Prefill batches.  A work-group of 4 waves, one per SIMD, computes TM = 64 MB tokens x 256
+// outputs of y, each wave 32 MB tokens x 128 outputs.  What bounds it: LDS traffic and the load
+// latency first, the chip's power then (1.8 GHz under this load).  128 x 128 wave tiles read 0.5
+// KiB of operands per MFMA (the 64 x 128 tiles of an 8-wave work-group 0.75 KiB, which with the
+// tile writes took every LDS cycle the MFMAs left); with one wave per SIMD the accumulators
+// (256 registers) and two sets of operands fit, so a step's MFMAs run with the next step's
+// operand reads and the loads between them, one barrier per 64 columns.  x tiles have a ring
+// of three stages and W tiles of two (160 KiB in all): stage s + 2 is requested while stage s
+// is multiplied.
+//
+// Stage s, four steps of 16 columns (the operands of a step are read during the step before):
+//   step 0       requests x(s + 2), into the buffer of x(s - 1)
+//   after step 2 this wave's reads of stage s have returned and its loads of stage s + 1 are
+//                complete (x(s + 2) may be pending); barrier
+//   step 3       requests W(s + 2), into the buffer of W(s); reads step 0 of stage s + 1
+// Stages past the end are requested as copies of the last one, into buffers nobody reads any
+// more, which keeps the counts constant.
+//
+// W is the MFMA's first operand, so a lane holds one token and its registers run over the
+// outputs: both members of a rotary pair are in one lane, the rotation needs no exchange, and
+// four consecutive outputs go to LDS as one 8-byte write.  The tile then leaves as whole
+// 16-byte chunks of contiguous rows.  (With the tile rounded and written by 2-byte stores and
+// rotated on the way out, the epilogue took 37 us of a tile's 129.)
+template <int D, bool POOL, int MB>
+__global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, int n_tokens, int hidden,
+    int n_out, int hq, int hkv, const float2* __restrict__ tab, uint16_t* __restrict__ q_out,
+    uint16_t* __restrict__ k_out, uint16_t* __restrict__ v_out, const int32_t* __restrict__ slots,
+    int64_t n_slots) {
+  constexpr int TM = 64 * MB;
+  constexpr int XB = TM * kKC * 2, WB = kTN * kKC * 2;  // bytes of an x and of a W stage
+  constexpr int XL = TM / 32, WL = kTN / 32;            // 1 KiB loads per wave of each (8 rows)
+  constexpr int kPitch = kTN * 2 + 16;
+  constexpr int kRing = 3 * XB + 2 * WB, kEnd = TM * kPitch + TM * 4;
+  __shared__ __attribute__((aligned(1024))) char smem[kRing > kEnd ? kRing : kEnd];  // rings, then y and slots
+  // Tile order.  Work-groups are dealt to the 8 XCDs in turn (b -> XCD b % 8) and each XCD has
+  // its own L2, so logical tile L = (b % 8) * (G / 8) + b / 8 gives every XCD a contiguous run
+  // of tiles; runs go over groups of kGroupTokens tokens output-tile by output-tile, so the
+  // ~32 tiles one XCD holds at a time share their x tiles and 8 (4) W tiles in its L2.
+  constexpr int kGroupM = kGroupTokens / TM;
+  const int n_tiles_n = n_out / kTN + (n_out % kTN ? 1 : 0);
+  const int n_tiles_m = n_tokens / TM + (n_tokens % TM ? 1 : 0);
+  const int b = blockIdx.x, full = gridDim.x & ~7;
+  const int L = b < full ? (b % 8) * (full / 8) + b / 8 : b;
+  const int group = L / (kGroupM * n_tiles_n), in_group = L % (kGroupM * n_tiles_n);
+  const int first_m = group * kGroupM, gm = min(n_tiles_m - first_m, kGroupM);
+  const int tile_m = first_m + in_group % gm, tile_n = in_group / gm;
+  const int t0 = tile_m * TM, n0 = tile_n * kTN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hg = lane >> 5;
+  const int row0 = (wave & 1) * (32 * MB);              // the wave's tokens of the tile
+  const int col0 = (wave >> 1) * 128;                   // the wave's 128 outputs
+
+  // ---- loads: piece i of a wave covers rows 32 i + 8 wave .. + 7 of a tile --------------------
+  uint32_t xofs[XL], wofs[WL];                          // byte offsets from the tile's first row
+  const int c_ld = (lane % 8) ^ (((8 * wave + lane / 8) >> 1) & 7);   // chunk of the row (the same for every i)
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {
+    const int t = min(t0 + 32 * i + 8 * wave + lane / 8, n_tokens - 1) - t0;
+    xofs[i] = static_cast<uint32_t>(t * hidden + c_ld * 8) * 2u;
+  }
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {
+    const int n = min(n0 + 32 * i + 8 * wave + lane / 8, n_out - 1) - n0;
+    wofs[i] = static_cast<uint32_t>(n * hidden + c_ld * 8) * 2u;
+  }
+  const uint16_t* xbase = x + static_cast<int64_t>(t0) * hidden;
+  const uint16_t* wbase = w + static_cast<int64_t>(n0) * hidden;
+  const int n_full = hidden / kKC, n_st = (hidden + kKC - 1) / kKC;
+  // the last stage of a hidden size that is no multiple of 64 holds 32 columns: its upper chunks
+  // repeat the lower ones (never used), so no lane reads past a row's end
+  const uint32_t hi64 = c_ld >= 4 ? 64u : 0u;
+  auto back = [&](int s) -> uint32_t { return s >= n_full ? hi64 : 0u; };
+  auto issue_x = [&](int s, int buf, int i) __attribute__((always_inline)) {
+    const int sc = min(s, n_st - 1);
+    load_lds16(xbase + sc * kKC, xofs[i] - back(sc), (lds_void*)(smem + buf * XB + (32 * i + 8 * wave) * 128));
+  };
+  auto issue_w = [&](int s, int i) __attribute__((always_inline)) {
+    const int sc = min(s, n_st - 1);
+    load_lds16(wbase + sc * kKC, wofs[i] - back(sc),
+               (lds_void*)(smem + 3 * XB + (s & 1) * WB + (32 * i + 8 * wave) * 128));
+  };
+
+  f32x16_t acc[MB][4];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x16_t{};
+  uint32_t xa[4], wa[4];                                // LDS bytes of this lane's operands of step ks
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const uint32_t c = ((2 * ks + hg) ^ ((l32 >> 1) & 7)) * 16;
+    xa[ks] = (row0 + l32) * 128 + c;
+    wa[ks] = 3 * XB + (col0 + l32) * 128 + c;
+  }
+  constexpr int NOP = MB + 4;                           // operands of a step: W blocks 0-3, then x blocks
+  bf16x8_t op[2][NOP];
+  auto rd = [&](int xo, int wo, int ks, int i) __attribute__((always_inline)) -> bf16x8_t {
+    return *reinterpret_cast<const bf16x8_t*>(smem + (i < 4 ? wa[ks] + wo + i * 4096 : xa[ks] + xo + (i - 4) * 4096));
+  };
+  // operands in the order the next step's MFMAs need them: the first x block, W, the other x blocks
+  constexpr int kOrder[8] = {4, 0, 1, 2, 3, 5, 6, 7};
+  // one step: 4 MB MFMAs, one operand read every other MFMA and, after that one, a load
+  auto step = [&](int cur, auto read, auto load) __attribute__((always_inline)) {
+    constexpr int N = 4 * MB, EV = N / NOP >= 2 ? 2 : 1;   // MFMAs per operand read
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int mb = n / 4, nb = n % 4;
+      acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[cur][nb], op[cur][4 + mb], acc[mb][nb], 0, 0, 0);
+      if (n % EV == 0 && n / EV < NOP) op[cur ^ 1][kOrder[n / EV]] = read(kOrder[n / EV]);
+      if (n % 2 == 1) load(n / 2);
+    }
+#pragma unroll
+    for (int n = 0; n < NOP; ++n) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (EV == 2) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < WL; ++i) issue_w(0, i);
+#pragma unroll
+  for (int i = 0; i < XL; ++i) issue_x(0, 0, i);
+#pragma unroll
+  for (int i = 0; i < XL; ++i) issue_x(1, 1, i);
+#pragma unroll
+  for (int i = 0; i < WL; ++i) issue_w(1, i);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XL + WL) : "memory");
+#pragma unroll
+  for (int i = 0; i < NOP; ++i) op[0][i] = rd(0, 0, 0, i);
+  int x3 = 0;                                           // s % 3
+  for (int s = 0; s < n_full; ++s) {
+    const int xo = x3 * XB, wo = (s & 1) * WB;
+    const int xn = x3 == 2 ? 0 : x3 + 1;
+    auto no_load = [](int) {};
+    step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 1, i); },
+         [&](int i) __attribute__((always_inline)) { if (i < XL) issue_x(s + 2, x3 == 0 ? 2 : x3 - 1, i); });
+    if constexpr (XL > 2 * MB) static_assert(XL <= 2 * MB, "every x load has its place in the step");
+    step(1, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 2, i); }, no_load);
+    step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 3, i); }, no_load);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XL) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    step(1, [&](int i) __attribute__((always_inline)) { return rd(xn * XB, WB - wo, 0, i); },
+         [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+           for (int k = 0; k < WL / (2 * MB); ++k) issue_w(s + 2, i * (WL / (2 * MB)) + k);
+         });
+    __builtin_amdgcn_sched_barrier(0);
+    x3 = xn;
+  }
+  if (n_st > n_full) {                                  // 32 columns left: two steps
+    const int xo = x3 * XB, wo = (n_full & 1) * WB;
+    step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 1, i); }, [](int) {});
+    step(1, [&](int i) __attribute__((always_inline)) { return op[0][i]; }, [](int) {});
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // no LDS write or read is in flight
+
+  // ---- epilogue: round, rotate, y tile to LDS ([token][output]) --------------------------------
+  // acc[mb][nb] register r: token row0 + 32 mb + l32, output col0 + 32 nb + 8 (r / 4) + 4 hg + r % 4
+  int32_t* tslot = reinterpret_cast<int32_t*>(smem + TM * kPitch);
+  if constexpr (POOL)
+    for (int e = tid; e < TM; e += 256) tslot[e] = t0 + e < n_tokens ? slots[t0 + e] : -1;
+  constexpr int PB = D / 64;                            // blocks of half a head: a pair is (nb, nb + PB)
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int row = row0 + 32 * mb + l32;
+    const float4* cs = reinterpret_cast<const float4*>(tab + static_cast<int64_t>(min(t0 + row, n_tokens - 1)) * (D / 2));
+    char* dst = smem + row * kPitch + (col0 + 4 * hg) * 2;
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {                    // the two pairs of blocks
+      const int lo = D == 128 ? pr : 2 * pr, hi = lo + PB;
+      const int i0 = D == 128 ? 32 * pr : 0;            // first angle of block lo
+      const bool rot = (n0 + col0 + 32 * lo) / D < hq + hkv;   // uniform
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        uint32_t a[2], c[2];                            // y of dims i .. i + 3 and of their partners
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          a[j] = pack_bf16(acc[mb][lo][4 * q4 + 2 * j], acc[mb][lo][4 * q4 + 2 * j + 1]);
+          c[j] = pack_bf16(acc[mb][hi][4 * q4 + 2 * j], acc[mb][hi][4 * q4 + 2 * j + 1]);
+        }
+        if (rot) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const float4 c2 = cs[(i0 + 8 * q4 + 4 * hg) / 2 + j];   // (cos, sin) of two angles
+            const float a0 = bf16_to_f32(a[j] & 0xFFFF), a1 = bf16_to_f32(a[j] >> 16);
+            const float b0 = bf16_to_f32(c[j] & 0xFFFF), b1 = bf16_to_f32(c[j] >> 16);
+            a[j] = pack_bf16(a0 * c2.x - b0 * c2.y, a1 * c2.z - b1 * c2.w);
+            c[j] = pack_bf16(b0 * c2.x + a0 * c2.y, b1 * c2.z + a1 * c2.w);
+          }
+        }
+        *reinterpret_cast<uint2*>(dst + (32 * lo + 8 * q4) * 2) = make_uint2(a[0], a[1]);
+        *reinterpret_cast<uint2*>(dst + (32 * hi + 8 * q4) * 2) = make_uint2(c[0], c[1]);
+      }
+    }
+  }
+  __syncthreads();
+  store_tile<D, POOL, false, TM, kTN, 256>(
+      smem, kPitch, t0, n_tokens, [&](int o) { return n0 + o; }, n_out, 0, [](int, int) -> const float4* { return nullptr; },
+      tslot, hq, hkv, q_out, k_out, v_out, n_slots);
+}
+
+// Decode steps and short questions.  The 256-token tiles would leave most compute units idle
+// (up to 256 tokens are 24 to 40 work-groups).  What bounds these calls is reading W once, so a
+// tile is narrow in outputs (TN = 32 NB) and tall enough for the tokens (TM = 32 MB), and its WV
+// waves split H: wave w takes the 64-column stages w, w + WV, ..  Every byte staged in LDS is read
+// by one wave only: each wave owns a ring of RING stages (its x and W rows) and waits for its
+// own loads, with no barrier in the loop; two to three work-groups of four waves share a
+// compute unit.  The partial sums (fp32) meet in LDS: the upper half of the waves hand theirs to
+// the lower half, whose sums are added in order.  A tile's columns are TN/2 dims below D/2 of
+// one head and their rotary partners D/2 above, so the rotation needs this tile only.  The
+// (cos, sin) pairs of the tile are computed here too, while the first stages are in flight: no
+// table pass.  64 tokens x 4096 x 6144: 14.9 us (3.4 TB/s of W), from 73.
+constexpr int kMetaMax = 256;     // cu_q entries staged in LDS; batches of more requests search global memory
+template <int D, bool POOL, int MB, int NB, int WV, int RING>
+__global__ __launch_bounds__(64 * WV, 2) void qkv_ksplit_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, int n_tokens, int hidden, int n_out, int hq,
+    int hkv, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ seq_lens, int n_reqs, double log2_theta,
+    uint16_t* __restrict__ q_out, uint16_t* __restrict__ k_out, uint16_t* __restrict__ v_out,
+    const int32_t* __restrict__ slots, int64_t n_slots) {
+  constexpr int TM = 32 * MB, TN = 32 * NB, ROWS = TM + TN, KC = kKC;
+  constexpr int STAGE = ROWS * KC * 2;               // bytes of one wave's stage: x rows, then W rows
+  constexpr int LOADS = STAGE / 1024;                 // 16-byte direct loads per thread per stage (16 rows each)
+  constexpr int kThr = 64 * WV, NS = WV / 2;          // NS: partial sums held in LDS at the end
+    constexpr int PP = TN + 4;                          // row pitch of the partial sums (floats)
+  constexpr int YP = TN * 2 + 16;                     // row pitch of the y tile (bytes)
+  constexpr int YOFS = NS * TM * PP * 4;              // after the loop: partial sums, y tile, (cos, sin)
+  constexpr int COFS = YOFS + TM * YP;
+  constexpr int END = COFS + TM * (TN / 2) * 8;
+  constexpr int RING_BYTES = WV * RING * STAGE;
+  constexpr int SMEM = END > RING_BYTES ? END : RING_BYTES;
+  constexpr int NCS = TM * (TN / 2) / kThr;           // (cos, sin) pairs per thread
+  static_assert(NCS * kThr == TM * (TN / 2) && COFS % 16 == 0, "(cos, sin) split");
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+  __shared__ int32_t meta[2][kMetaMax];               // cu_q, seq_lens
+  __shared__ int32_t tslot[TM];
+  const int n_tiles_n = n_out / TN, n_tiles_m = (n_tokens + TM - 1) / TM;
+  // every XCD (b % 8) gets a contiguous run of tiles, token tiles fastest: tiles that share W rows
+  // run on one XCD
+  const int b = blockIdx.x, full = gridDim.x & ~7;
+  const int L = b < full ? (b % 8) * (full / 8) + b / 8 : b;
+  const int tile_n = L / n_tiles_m, tile_m = L % n_tiles_m;
+  if (tile_n >= n_tiles_n) return;
+  const int t0 = tile_m * TM;
+  const int head = tile_n / (D / TN), part = tile_n % (D / TN);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hg = lane >> 5;
+  // dim of local column o within the head: o < TN/2 below D/2, its partner TN/2 columns further on
+  auto dim_of = [&](int o) { return o < TN / 2 ? part * (TN / 2) + o : D / 2 + part * (TN / 2) + o - TN / 2; };
+
+  // piece i of a stage covers its rows 8 i .. 8 i + 7: the tile's tokens, then its W rows
+  uint32_t ofs[LOADS];                                // byte offsets of this lane's 16 bytes at column 0
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    const int row = 8 * i + lane / 8;
+    const int c = (lane % 8) ^ ((row >> 1) & 7);
+    const int r = row < TM ? min(t0 + row, n_tokens - 1) - t0 : dim_of(row - TM);
+    ofs[i] = static_cast<uint32_t>(r * hidden + c * 8) * 2u;
+  }
+  const uint16_t* xbase = x + static_cast<int64_t>(t0) * hidden;
+  const uint16_t* wbase = w + static_cast<int64_t>(head) * D * hidden;
+  char* ring = smem + wave * (RING * STAGE);
+  const int n_full = hidden / KC, n_st = (hidden + KC - 1) / KC;
+  const int cnt = n_st > wave ? (n_st - wave + WV - 1) / WV : 0;    // this wave's stages: wave, wave + WV, ..
+  auto issue = [&](int j) {
+    char* st = ring + (j % RING) * STAGE;
+    const int s = j * WV + wave;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      // a last stage of 32 columns: its upper chunks repeat the lower ones (never used)
+      const int c = (lane % 8) ^ (((8 * i + lane / 8) >> 1) & 7);
+      load_lds16((i < TM / 8 ? xbase : wbase) + s * KC, ofs[i] - (s >= n_full && c >= 4 ? 64u : 0u),
+                 (lds_void*)(st + i * 1024));
+    }
+  };
+
+  // ---- the batch's request boundaries to LDS, then the first stages ------------------------
+  const bool rot = head < hq + hkv;                   // uniform: Q or K
+  const bool staged = n_reqs < kMetaMax;              // cu_q has n_reqs + 1 entries
+  if (rot && staged) {
+    if (wave < kMetaMax / 64) {
+      const int e = wave * 64 + lane;
+      load_lds4(cu_q + min(e, n_reqs), (lds_void*)(&meta[0][wave * 64]));
+      load_lds4(seq_lens + min(e, n_reqs - 1), (lds_void*)(&meta[1][wave * 64]));
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < RING; ++j)
+    if (j < cnt) issue(j);
+  float2 cs_reg[NCS];
+  if (rot) {
+    // the boundaries were requested first: they are here once at most the ring's loads are pending
+    if (cnt >= RING) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(RING * LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    constexpr double kTwoPi = 6.283185307179586476925;
+#pragma unroll
+    for (int k = 0; k < NCS; ++k) {
+      const int e = tid + k * kThr;
+      const int row = e / (TN / 2), i = e % (TN / 2);
+      const int t = min(t0 + row, n_tokens - 1);
+      auto cu = [&](int r) { return staged ? meta[0][r] : cu_q[r]; };
+      int lo = 0, hi = n_reqs - 1;                    // request of token t: the last r with cu_q[r] <= t
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (cu(mid) <= t) lo = mid; else hi = mid - 1;
+      }
+      const int64_t len = staged ? meta[1][lo] : seq_lens[lo];
+      const int64_t p = len - (cu(lo + 1) - cu(lo)) + (t - cu(lo));
+      // theta^(-2 i / D) as a power of two: its rounding (exponents up to ~2^5) moves an angle by
+      // under 1e-14 of itself, far below the fp32 sine and cosine
+      const double f = exp2(log2_theta * (-2.0 * (part * (TN / 2) + i) / D));
+      const double a = static_cast<double>(p) * f;
+      const double r = std::fma(-std::floor(a / kTwoPi), kTwoPi, a);
+      float sn, cs;
+      sincosf(static_cast<float>(r), &sn, &cs);
+      cs_reg[k] = make_float2(cs, sn);
+    }
+  }
+
+  // ---- the loop over this wave's columns -----------------------------------------------------
+  f32x16_t acc[MB][NB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x16_t{};
+  for (int j = 0; j < cnt; ++j) {
+    // stage j is complete when at most the RING - 1 newer stages are pending (loads return in order)
+    if (j + RING <= cnt) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 1) * LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const char* st = ring + (j % RING) * STAGE;
+    bf16x8_t a[KC / 16][MB], bq[KC / 16][NB];
+#pragma unroll
+    for (int ks = 0; ks < KC / 16; ++ks) {
+      const int c = (ks * 2 + hg) ^ ((l32 >> 1) & 7);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) a[ks][mb] = *reinterpret_cast<const bf16x8_t*>(st + (mb * 32 + l32) * 128 + c * 16);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        bq[ks][nb] = *reinterpret_cast<const bf16x8_t*>(st + (TM + nb * 32 + l32) * 128 + c * 16);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the stage is read: it may be overwritten
+    if (j + RING < cnt) issue(j + RING);
+    const int n_ks = j * WV + wave < n_full ? KC / 16 : KC / 32;
+#pragma unroll
+    for (int ks = 0; ks < KC / 16; ++ks)
+      if (ks < KC / 32 || ks < n_ks)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][mb], bq[ks][nb], acc[mb][nb], 0, 0, 0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // no wave's ring is in use any more
+
+  // ---- sum over the waves: the upper half into the lower, then those sums in order -----------
+  float* sums = reinterpret_cast<float*>(smem) + (wave % NS) * (TM * PP);
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          f(sums[(mb * 32 + (r / 4) * 8 + hg * 4 + (r % 4)) * PP + nb * 32 + l32], acc[mb][nb][r]);
+  };
+  float2* cs_tab = reinterpret_cast<float2*>(smem + COFS);
+  if (rot)
+#pragma unroll
+    for (int k = 0; k < NCS; ++k) cs_tab[tid + k * kThr] = cs_reg[k];
+  if (wave >= NS) each([](float& s, float v) { s = v; });
+  if constexpr (POOL)
+    if (tid < TM) tslot[tid] = t0 + tid < n_tokens ? slots[t0 + tid] : -1;
+  __syncthreads();
+  if (wave < NS) each([](float& s, float v) { s = v + s; });
+  __syncthreads();
+  const float* s0 = reinterpret_cast<const float*>(smem);
+  for (int e = tid; e < TM * TN / 4; e += kThr) {
+    const int row = e / (TN / 4), c = (e % (TN / 4)) * 4;
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(s0 + row * PP + c);
+#pragma unroll
+    for (int g = 1; g < NS; ++g) v += *reinterpret_cast<const f32x4_t*>(s0 + g * (TM * PP) + row * PP + c);
+    uint2 y;
+    y.x = pack_bf16(v[0], v[1]);
+    y.y = pack_bf16(v[2], v[3]);
+    *reinterpret_cast<uint2*>(smem + YOFS + row * YP + c * 2) = y;
+  }
+  __syncthreads();
+  store_tile<D, POOL, true, TM, TN, kThr>(
+      smem + YOFS, YP, t0, n_tokens, [&](int o) { return head * D + dim_of(o); }, n_out, TN / 2,
+      [&](int row, int i) { return reinterpret_cast<const float4*>(&cs_tab[row * (TN / 2) + i - part * (TN / 2)]); },
+      tslot, hq, hkv, q_out, k_out, v_out, n_slots);
+}
+
 }  // namespace
 
 namespace {
+
+// Which kernel and tile a call takes, by its sizes alone (never by where K and V go, so that
+// arckv_qkv_rope and arckv_qkv_rope_to_pool give the same bits).  us per call, 32 / 8 heads of
+// 128 and hidden 4096 unless stated, against the 256 x 256 tiles that served every size before:
+//   T <= 32   eight waves per 32 x 32 tile when every tile has its own compute unit: 11.0 at T =
+//             32 (four waves, two tiles per unit: 11.9; before: 69); else four waves: hidden
+//             8192, 320 tiles: 44.7 against 46.1
+//   T <= 64   four waves, 32 x 32: 14.9 at T = 64 (64 x 32: 15.8; before: 73)
+//   up to 3.5 64 x 64 tiles per compute unit: 64 x 64 where they fill most of the chip and H is
+//             long enough to outweigh their reduction (T = 256: 30.7, hidden 5120: 38.7 against
+//             46.9 with 64 x 32; before 97 and 137), else 64 x 32 (hidden 1024, 3072 outputs,
+//             T = 256: 10.2 against 13.5).  Past that the prefill kernel's reuse wins: hidden 8192,
+//             T = 512 (5 tiles per unit): 129 against 149; hidden 5120, T = 512 (3.5): 83 against 77
+//   prefill   128-token tiles when they need fewer rounds of the chip for their 0.6 of a 256-token
+//             tile's time: hidden 5120, T = 907: 89 against 117; T = 2000: 173 against 136
+enum class QkvRoute { kK32x32Wide, kK32x32, kK64x32, kK64x64, kG128, kG256 };
+constexpr int64_t kUnits = 256;   // compute units of an MI355X
+QkvRoute qkv_route(int64_t n_tokens, int64_t hidden, int64_t n_out) {
+  auto tiles = [&](int64_t m, int64_t n) { return ((n_tokens + m - 1) / m) * ((n_out + n - 1) / n); };
+  if (n_tokens <= 32 && tiles(32, 32) <= kUnits) return QkvRoute::kK32x32Wide;
+  if (n_tokens <= 64) return QkvRoute::kK32x32;
+  if (2 * tiles(64, 64) <= 7 * kUnits)
+    return hidden > 2048 && 4 * tiles(64, 64) >= 3 * kUnits ? QkvRoute::kK64x64 : QkvRoute::kK64x32;
+  auto rounds = [&](int64_t m) { return (tiles(m, kTN) + kUnits - 1) / kUnits; };
+  return 3 * rounds(128) < 5 * rounds(256) ? QkvRoute::kG128 : QkvRoute::kG256;
+}
 
 // Shared by arckv_qkv_rope and arckv_qkv_rope_to_pool: pool == true writes K and V into the
 // pools k_dst / v_dst (num_blocks blocks) at slots.
@@ -332,14 +633,14 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
   if (head_dim != 64 && head_dim != 128)
     return arckv::fail(ARCKV_EUNSUPPORTED, "%s: head_dim %d not in {64,128}", fn, head_dim);
   const int64_t n_out = static_cast<int64_t>(num_q_heads + 2 * num_kv_heads) * head_dim;
-  if (hidden % kKB != 0 || hidden > (1 << 22) || n_out % 128 != 0)   // (32-bit load offsets in a tile)
+  if (hidden % 32 != 0 || hidden > (1 << 22) || n_out % 128 != 0)   // (32-bit load offsets in a tile)
     return arckv::fail(ARCKV_EUNSUPPORTED,
                        "%s: hidden %d must be a multiple of %d (at most 2^22) and the %lld outputs of 128",
-                       fn, hidden, kKB, (long long)n_out);
+                       fn, hidden, 32, (long long)n_out);
   if (pool && (num_blocks < 1 || num_blocks > (int64_t{1} << 27)))
     return arckv::fail(ARCKV_EINVAL, "%s: num_blocks %lld", fn, (long long)num_blocks);
   if (n_tokens == 0) return ARCKV_OK;
-  if (n_tokens > INT32_MAX - kTM || n_out > INT32_MAX || n_reqs < 1 ||
+  if (n_tokens > INT32_MAX - 256 || n_out > INT32_MAX || n_reqs < 1 ||
       static_cast<int64_t>(hidden) * n_tokens > (int64_t{1} << 40))
     return arckv::fail(ARCKV_EINVAL, "%s: %lld tokens, %lld outputs, %d requests", fn,
                        (long long)n_tokens, (long long)n_out, n_reqs);
@@ -358,8 +659,6 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
   auto* s = static_cast<hipStream_t>(stream);
   auto* tab = static_cast<float2*>(workspace);
   const dim3 tgrid(static_cast<unsigned>(std::min<int64_t>(kTableBlocks, (n_tokens * (head_dim / 2) + 255) / 256)));
-  const int64_t n_tiles_n = (n_out + kTN - 1) / kTN;
-  const dim3 grid(static_cast<unsigned>(n_tiles_n * ((n_tokens + kTM - 1) / kTM)));
   auto* xp = static_cast<const uint16_t*>(x);
   auto* wp = static_cast<const uint16_t*>(w_qkv);
   auto* q = static_cast<uint16_t*>(q_out);
@@ -370,9 +669,32 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
   auto go = [&](auto d_tag, auto pool_tag) {
     constexpr int D = decltype(d_tag)::value;
     constexpr bool P = decltype(pool_tag)::value;
-    hipLaunchKernelGGL(rope_table_kernel<D>, tgrid, dim3(256), 0, s, n_tokens, cu_q, seq_lens, n_reqs, rope_theta, tab);
-    hipLaunchKernelGGL((qkv_gemm_rope_kernel<D, P>), grid, dim3(kThreads), 0, s, xp, wp, T, hidden, N,
-                       num_q_heads, num_kv_heads, tab, q, k, v, slots, n_slots);
+    auto ksplit = [&](auto mb, auto nb, auto wv, auto ring) {
+      constexpr int MB = decltype(mb)::value, NB = decltype(nb)::value, WV = decltype(wv)::value;
+      const dim3 grid(static_cast<unsigned>((n_out / (32 * NB)) * ((n_tokens + 32 * MB - 1) / (32 * MB))));
+      hipLaunchKernelGGL((qkv_ksplit_kernel<D, P, MB, NB, WV, decltype(ring)::value>), grid, dim3(64 * WV), 0, s, xp,
+                         wp, T, hidden, N, num_q_heads, num_kv_heads, cu_q, seq_lens, n_reqs, std::log2(rope_theta), q, k,
+                         v, slots, n_slots);
+    };
+    auto gemm = [&](auto mb) {
+      constexpr int MB = decltype(mb)::value;
+      const dim3 grid(static_cast<unsigned>(((n_out + kTN - 1) / kTN) * ((n_tokens + 64 * MB - 1) / (64 * MB))));
+      hipLaunchKernelGGL(rope_table_kernel<D>, tgrid, dim3(256), 0, s, n_tokens, cu_q, seq_lens, n_reqs, rope_theta, tab);
+      hipLaunchKernelGGL((qkv_gemm_rope_kernel<D, P, MB>), grid, dim3(256), 0, s, xp, wp, T, hidden, N,
+                         num_q_heads, num_kv_heads, tab, q, k, v, slots, n_slots);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    switch (qkv_route(n_tokens, hidden, n_out)) {
+      case QkvRoute::kK32x32Wide: ksplit(I1{}, I1{}, I8{}, I2{}); break;
+      case QkvRoute::kK32x32: ksplit(I1{}, I1{}, I4{}, I2{}); break;
+      case QkvRoute::kK64x32: ksplit(I2{}, I1{}, I4{}, I1{}); break;
+      case QkvRoute::kK64x64: ksplit(I2{}, I2{}, I4{}, I1{}); break;
+      case QkvRoute::kG128: gemm(I2{}); break;
+      case QkvRoute::kG256: gemm(I4{}); break;
+    }
   };
   using D64 = std::integral_constant<int, 64>;
   using D128 = std::integral_constant<int, 128>;

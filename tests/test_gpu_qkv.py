@@ -198,3 +198,51 @@ def test_qkv_rope_to_pool_equals_projection_then_scatter(kind, reqs, hidden, hq,
     assert np.array_equal(bits(vp_a), bits(vp_b)), "V pool differs"
     written = int((bits(kp_b) != 0xFFFF).any(axis=(1, 3)).sum())
     assert written > 0
+
+
+# The kernels are chosen by T, hidden and the outputs; each case sits at an edge of its kernel's
+# range or tiles.  hidden = 32 mod 64 leaves half a stage at the end.
+ROUTES = [
+    ("32x32 tiles, 8 waves", [(9, 0), (70, 48)], 1056, 8, 2, 128),
+    ("32x32 tiles, 8 waves, one full", [(5000, 4968)], 512, 4, 1, 64),
+    ("32x32 tiles, 8 waves, fewer stages than waves", [(40, 20)], 96, 4, 1, 64),
+    ("32x32 tiles, 4 waves, first of range", [(33, 0)], 544, 4, 2, 128),
+    ("32x32 tiles, 4 waves, last of range", [(100 + i, 99 + i) for i in range(64)], 4096, 4, 2, 64),
+    ("64x32 tiles, first of range", [(65, 0)], 160, 4, 2, 128),
+    ("64x32 tiles, more requests than are staged", [(1 + 7 * i, 7 * i) for i in range(300)], 256, 4, 2, 64),
+    ("64x32 tiles, an empty request", [(50, 0), (32, 32), (90, 10)], 1056, 8, 2, 128),
+    ("64x64 tiles", [(40, 3), (900, 850)], 2080, 32, 8, 128),
+    ("64x64 tiles, d 64", [(129, 0)], 2112, 96, 48, 64),
+    ("128-token tiles, ragged", [(2390, 0)], 96, 8, 2, 128),
+    ("128-token tiles, d 64, half an output tile", [(2301, 1), (257, 100)], 64, 22, 2, 64),
+    ("256-token tiles, ragged", [(6001, 0), (500, 170)], 160, 8, 2, 128),
+    ("256-token tiles, d 64, one stage", [(6000, 0), (331, 1)], 32, 20, 2, 64),
+]
+
+
+@pytest.mark.parametrize("what,reqs,hidden,hq,hkv,d", ROUTES, ids=[r[0] for r in ROUTES])
+def test_qkv_rope_every_kernel(what, reqs, hidden, hq, hkv, d):
+    """Rows against the oracle, and the pool variant bit for bit against those rows."""
+    print_case(f"{what}: hidden={hidden} hq={hq} hkv={hkv} d={d}")
+    r = run(reqs, hidden, hq, hkv, d, seed=31 + hidden)
+    check(r, hq, hkv, d)
+    T = r["q"].shape[0]
+    nblk = sum((L + 15) // 16 for L, _ in reqs) + 6
+    slots_h = slot_pattern("skips", reqs, nblk, np.random.default_rng(T))
+    slots = torch.from_numpy(slots_h).to(DEV)
+    q = torch.full_like(r["q"], float("nan"))
+    kp = torch.full((nblk, hkv, 16, d), -1, dtype=torch.int16, device=DEV)
+    vp = torch.full((nblk, hkv, d, 16), -1, dtype=torch.int16, device=DEV)
+    kp_ref, vp_ref = kp.clone(), vp.clone()
+    ws = torch.empty(4 * T * d, dtype=torch.uint8, device=DEV)
+    ak.qkv_rope_to_pool(r["x"], r["w"], torch.from_numpy(r["cu"]).to(DEV), torch.from_numpy(r["sl"]).to(DEV), hq, hkv,
+                        THETA, q, kp, vp, slots, ws)
+    ok = np.flatnonzero((slots_h >= 0) & (slots_h < nblk * 16))
+    s = torch.from_numpy(slots_h[ok].astype(np.int64)).to(DEV)
+    rows = torch.from_numpy(ok).to(DEV)
+    kp_ref[s // 16, :, s % 16, :] = r["k"].view(torch.int16)[rows]
+    vp_ref[s // 16, :, :, s % 16] = r["v"].view(torch.int16)[rows]
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(q), bits(r["q"])), "Q differs"
+    assert np.array_equal(bits(kp), bits(kp_ref)), "K pool differs"
+    assert np.array_equal(bits(vp), bits(vp_ref)), "V pool differs"
