@@ -131,6 +131,12 @@ __device__ __forceinline__ void load_lds16_s(const void* base, uint32_t ofs, lds
                : "memory", "m0");
 }
 
+// 4 bytes per lane (lane l writes LDS bytes [M0 + 4 l, M0 + 4 l + 4)).
+__device__ __forceinline__ void load_lds4(const void* g, lds_void* l) {
+  const uint32_t m = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(l));
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(m) : "memory", "m0");
+}
+
 // Narrow tiles (128 query columns: short suffixes and decode-like batches) run as persistent
 // work-groups.  The host plan hands every work-group a list of up to kListItems items (its live
 // items first, then idle padding), balanced so that the lists of a launch carry about equal
@@ -627,8 +633,15 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // step 2t-1, the barrier before tile t's first reader (group 0's M(t-1)).  They overwrite the
 // ring stage of tile t-4, whose last reader (group 1's M(t-4)) ran in half step 2t-5.  The block
 // numbers come from a copy of the item's block-table slice in LDS, read one tile ahead.
+//
+// Short items are bound by what surrounds the steps (1.6 us each at D = 128): the round trips
+// before the first MFMA, the output stores, and the next work-group's start.  The prologue asks
+// for everything in two dependent trips and the outputs leave as whole rows: 12 -> 8 us per item,
+// 16 conversation turns (1816 items of 31 steps) 432 -> 419 us.  At D = 64 (80 KiB of LDS, half
+// the MFMAs per exponential) two work-groups share a compute unit, four waves per SIMD, so one
+// item's prologue runs beside the other's steps: 12 uncached prompts of 1100 tokens 78 -> 68 us.
 template <int D, int G>
-__global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
+__global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
     const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
     const int32_t* __restrict__ block_tables, int bt_stride,
@@ -645,7 +658,10 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
   constexpr int LDB = kThreads * 16;             // bytes one load instruction moves per WG
   constexpr int BLK_BYTES = 16 * D * 2;          // one block of one head, K or V
   constexpr int NOP = 4 * DM + 2 * KSTEPS;       // MFMAs of a full M phase
-  constexpr int PD = 3;                          // LDS operands in flight ahead of their MFMA (3 measured 1-2 % faster than 2, 4, 5 or 6)
+  // LDS operands in flight ahead of their MFMA.  D = 128: 3 measured 1-2 % faster than 2, 4, 5
+  // or 6.  D = 64: four waves per SIMD hide the reads, and 1 spills least (12 uncached prompts of
+  // 1100 tokens, 16 heads: 67.6 us, 68.6 with 3; 32 turns of 300 tokens on 4 / 2 heads: 81.8, 85.4).
+  constexpr int PD = D == 64 ? 1 : 3;
   static_assert(NLD >= 1 && TILE % LDB == 0, "tile must be a multiple of one WG-wide load");
   constexpr int kTbl = arckv::kMaxItemKeys / 16;  // block-table entries of one work item
   __shared__ __attribute__((aligned(1024))) char smem[kStages * 2 * TILE];  // stage s: K, then V
@@ -660,26 +676,32 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2;
   const int l32 = lane & 31, hg = lane >> 5;
+  // The physical blocks of the first tiles' pieces are looked up together with the request's
+  // lengths (bounded here by the item's own key range): one scalar round trip for all of them.
+  constexpr int kFirst = kStages - 1;
+  const int32_t* bt = block_tables + static_cast<int64_t>(w.req) * bt_stride;
+  const int b_lo = max(w.kv_start, 0) >> 4;
+  const int b_hi = min(max((w.kv_end + kBK - 1) / kBK, 0) * (kBK / 16), bt_stride);   // past the item's last tile
+  int32_t first_ph[kFirst][NLD];
+#pragma unroll
+  for (int k = 0; k < kFirst; ++k)
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int b = b_lo + k * (kBK / 16) + (i * LDB + wave * 1024) / BLK_BYTES;
+      first_ph[k][i] = b < b_hi ? bt[b] : 0;
+    }
   const int q0 = cu_q[w.req];
   const int S = cu_q[w.req + 1] - q0;
   const int L = seq_lens[w.req];
   const int P = L - S;
   const int ncols = S * G;
-  const int32_t* bt = block_tables + static_cast<int64_t>(w.req) * bt_stride;
   const int nblk = min((L + 15) >> 4, bt_stride);
 
-  // ---- this lane's query column and its Q^T operands ------------------------------------
+  // ---- this lane's query column ----------------------------------------------------------
   const int col = w.col_start + wave * 32 + l32;
-  const int tok = col / G, g = col % G;
+  const int tok = col / G;
   const bool cval = col < ncols && (q0 + tok) < n_q;
   const int pos = cval ? P + tok : -1;
-  bf16x8_t qf[KSTEPS];
-  {
-    const int64_t qrow = static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + g;
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks)
-      qf[ks] = cval ? *reinterpret_cast<const bf16x8_t*>(q + qrow * D + ks * 16 + hg * 8) : bf16x8_t{};
-  }
 
   const int last_col = min(w.col_start + kCols, ncols) - 1;
   const int wg_max_pos = P + last_col / G;
@@ -707,15 +729,7 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
   // a wait for the scalar memory round trip at every tile (and, while one is in flight, full
   // waits on every LDS operand read, since scalar loads may return out of order).  The host
   // plan keeps every item within kMaxItemKeys keys, so n_tbl <= kTbl.
-  const int b_lo = kv_lo >> 4;
   const int n_tbl = max(0, min(min(nblk - b_lo, ntiles * (kBK / 16)), kTbl));
-  constexpr int kTblPer = kTbl / kThreads;
-  int32_t tbl_v[kTblPer];
-#pragma unroll
-  for (int k = 0; k < kTblPer; ++k) {
-    const int e = tid + k * kThreads;
-    tbl_v[k] = e < n_tbl ? bt[b_lo + e] : 0;
-  }
   // Lane i < NLD of next_v holds the physical block of the next tile's piece i, looked up one
   // tile ahead with a lane-dependent address (so it stays in a vector register and its LDS
   // read has long returned when readlane takes it).
@@ -737,20 +751,18 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
       load_lds16_s(v_pool + base, static_cast<uint32_t>(v_off[i]) * 2u, (lds_void*)(st + TILE + i * LDB + wave * 1024));
     }
   };
-  // tiles issued before the table is in LDS read their entries from the global table
-  auto load_tile_global = [&](int tile) {
+  // the first tiles are issued before the table is in LDS
+  auto issue_first = [&](int tile) {
     int32_t ph[NLD];
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int b = b_lo + ((tile * kBK) >> 4) + blk_of[i];
-      ph[i] = b < nblk ? bt[b] : 0;
-    }
+    for (int i = 0; i < NLD; ++i) ph[i] = b_lo + tile * (kBK / 16) + (i * LDB + wave * 1024) / BLK_BYTES < nblk ? first_ph[tile][i] : 0;
     issue(tile, ph);
   };
 
   f32x16_t o[DM];
 #pragma unroll
   for (int md = 0; md < DM; ++md) o[md] = f32x16_t{};
+  bf16x8_t qf[KSTEPS];              // Q^T operands of this lane's column
   f32x16_t sacc[2];                 // S^T of one tile: 2 blocks of 32 keys x this wave's columns
   uint32_t pw[4][4];                // P^T operands: 4 blocks of 16 keys, bf16 pairs
   float m_run = -INFINITY, l_run = 0.f;
@@ -933,21 +945,39 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
   auto barrier_wait = [&](int) {   // the one tile issued after the awaited one may be in flight
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
   };
-  // The table, the Q loads and tile 0 (read in half step 0): one vmcnt(0) covers them (an
-  // instruction the compiler's wait insertion understands, so it adds none of its own before
-  // Q is used).  Tiles 1 and 2 go out after it, to arrive while S(0) is computed: the waits
-  // in the loop already leave one tile in flight beyond the one a phase reads.  The barrier
-  // publishes the table without waiting for those loads.
-  if (ntiles > 0) load_tile_global(0);
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-  for (int t = 1; t < kStages - 1; ++t)
-    if (t < ntiles) load_tile_global(t);
+  // Prologue: the block table, this wave's queries and tiles 0 and 1 are requested together, all
+  // straight into LDS.  The queries (this wave's 32 columns, rows of D; chunk c of row r at
+  // c ^ fk(r)) land in the stages of tiles 2 and 3 and are read from there by this wave only;
+  // tile 2 goes out once every wave has read its own.  (Loaded into registers by lanes a row
+  // apart, and with the later tiles waiting behind them, the queries cost 2 us more per item.)
+  constexpr int QROWS = 512 / D;                       // query rows per load instruction
+  constexpr int QLD = 32 / QROWS;
+  char* qst = smem + 2 * (2 * TILE) + wave * (32 * D * 2);
+  if (ntiles > 0) {
 #pragma unroll
-  for (int k = 0; k < kTblPer; ++k) {
-    const int e = tid + k * kThreads;
-    if (e < n_tbl) tbl[e] = tbl_v[k];
+    for (int k = 0; k < kTbl / kThreads; ++k) {
+      const int e = k * kThreads + wave * 64;          // wave-uniform
+      if (e < n_tbl) load_lds4(bt + b_lo + min(e + lane, n_tbl - 1), (lds_void*)(tbl + e));
+    }
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+      const int r = i * QROWS + lane / (D / 8);
+      const int c = w.col_start + wave * 32 + r;       // columns past the request load row 0, never used
+      const bool ok = c < ncols && (q0 + c / G) < n_q;
+      const int64_t row = ok ? static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G : 0;
+      load_lds16(q + row * D + (((lane % (D / 8)) ^ fk<D>(r)) * 8), (lds_void*)(qst + i * 1024));
+    }
+    issue_first(0);
+    issue_first(1);                                    // past the key range: block 0 into a stage nobody reads
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NLD) : "memory");
   }
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+  for (int ks = 0; ks < KSTEPS; ++ks)
+    qf[ks] = cval ? *reinterpret_cast<const bf16x8_t*>(qst + l32 * (2 * D) + (((2 * ks + hg) ^ fk<D>(l32)) * 16))
+                  : bf16x8_t{};
+  // table, queries and tile 0 are here (tile 1 may be pending), and every wave has read its queries
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
+  if (ntiles > 0) issue_first(2);
   fetch_next(kStages - 1);
   if (ntiles > 0) {
     const int e_tile = (L - kv_lo + kBK - 1) / kBK - 1;   // the tile holding key L - 1
@@ -999,9 +1029,12 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
   const float lse = lt > 0.f ? m_run + __log2f(lt) : -INFINITY;
 #pragma unroll
   for (int md = 0; md < DM; ++md) o[md] *= inv;
-  if (!cval) return;
   if (w.slot < 0) {
-    uint16_t* dst = out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + g) * D;
+    // Through LDS ([column][dim], this wave's own rows), so that rows leave as whole 16-byte
+    // chunks: 8-byte stores of lanes a row apart took 4 us per item.
+    constexpr int EP = 2 * D + 16;                     // row pitch in bytes
+    asm volatile("s_barrier" ::: "memory");            // no wave reads the ring any more
+    char* ep = smem + wave * (32 * EP);
 #pragma unroll
     for (int md = 0; md < DM; ++md)
 #pragma unroll
@@ -1009,10 +1042,19 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_pp_kernel(
         f32x4_t v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
-        *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * hg) = __builtin_convertvector(v, bf16x4_t);
+        *reinterpret_cast<bf16x4_t*>(ep + l32 * EP + (md * 32 + 8 * r4 + 4 * hg) * 2) = __builtin_convertvector(v, bf16x4_t);
       }
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+      const int r = i * QROWS + lane / (D / 8), ch = lane % (D / 8);
+      const int c = w.col_start + wave * 32 + r;
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(ep + r * EP + ch * 16);
+      if (c < ncols && (q0 + c / G) < n_q)
+        *reinterpret_cast<u32x4_t*>(out + (static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G) * D + ch * 8) = v;
+    }
     return;
   }
+  if (!cval) return;
   if (w.slot >= ws_slots) return;
   const int local = wave * 32 + l32;
   float* po = ws_o + (static_cast<int64_t>(w.slot) * kCols + local) * D;
