@@ -638,10 +638,12 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // before the first MFMA, the output stores, and the next work-group's start.  The prologue asks
 // for everything in two dependent trips and the outputs leave as whole rows: 12 -> 8 us per item,
 // 16 conversation turns (1816 items of 31 steps) 432 -> 419 us.  At D = 64 (80 KiB of LDS, half
-// the MFMAs per exponential) two work-groups share a compute unit, four waves per SIMD, so one
+// the MFMAs per exponential) two work-groups can share a compute unit, four waves per SIMD, so one
 // item's prologue runs beside the other's steps: 12 uncached prompts of 1100 tokens 78 -> 68 us.
-template <int D, int G>
-__global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
+// PAIRED is that build (128 registers).  With no more items than units it would let the dispatcher
+// put two on one unit and leave another idle (3 turns on 2000 cached tokens: 57 us against 49).
+template <int D, int G, bool PAIRED>
+__global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
     const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
     const int32_t* __restrict__ block_tables, int bt_stride,
@@ -658,10 +660,10 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
   constexpr int LDB = kThreads * 16;             // bytes one load instruction moves per WG
   constexpr int BLK_BYTES = 16 * D * 2;          // one block of one head, K or V
   constexpr int NOP = 4 * DM + 2 * KSTEPS;       // MFMAs of a full M phase
-  // LDS operands in flight ahead of their MFMA.  D = 128: 3 measured 1-2 % faster than 2, 4, 5
-  // or 6.  D = 64: four waves per SIMD hide the reads, and 1 spills least (12 uncached prompts of
-  // 1100 tokens, 16 heads: 67.6 us, 68.6 with 3; 32 turns of 300 tokens on 4 / 2 heads: 81.8, 85.4).
-  constexpr int PD = D == 64 ? 1 : 3;
+  // LDS operands in flight ahead of their MFMA.  3 measured 1-2 % faster than 2, 4, 5 or 6.  PAIRED:
+  // four waves per SIMD hide the reads, and 1 spills least (the 12 prompts: 67.6 us, 68.6 with 3;
+  // 32 turns of 300 tokens on 4 / 2 heads: 81.8 us, 85.4 with 3).
+  constexpr int PD = PAIRED ? 1 : 3;
   static_assert(NLD >= 1 && TILE % LDB == 0, "tile must be a multiple of one WG-wide load");
   constexpr int kTbl = arckv::kMaxItemKeys / 16;  // block-table entries of one work item
   __shared__ __attribute__((aligned(1024))) char smem[kStages * 2 * TILE];  // stage s: K, then V
@@ -959,6 +961,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
       const int e = k * kThreads + wave * 64;          // wave-uniform
       if (e < n_tbl) load_lds4(bt + b_lo + min(e + lane, n_tbl - 1), (lds_void*)(tbl + e));
     }
+    if (w.col_start + wave * 32 < ncols)               // wave-uniform: a wave without a column loads none
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
       const int r = i * QROWS + lane / (D / 8);
@@ -968,16 +971,26 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
       load_lds16(q + row * D + (((lane % (D / 8)) ^ fk<D>(r)) * 8), (lds_void*)(qst + i * 1024));
     }
     issue_first(0);
-    issue_first(1);                                    // past the key range: block 0 into a stage nobody reads
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NLD) : "memory");
+    // With a second tile, tiles 1 and 2 always go out (2 past the key range: block 0 into a stage
+    // nobody reads), so that the loop's waits count the same loads; a single tile needs neither.
+    if (ntiles > 1) {
+      issue_first(1);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NLD) : "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NLD) : "memory");
+    }
   }
 #pragma unroll
   for (int ks = 0; ks < KSTEPS; ++ks)
     qf[ks] = cval ? *reinterpret_cast<const bf16x8_t*>(qst + l32 * (2 * D) + (((2 * ks + hg) ^ fk<D>(l32)) * 16))
                   : bf16x8_t{};
   // table, queries and tile 0 are here (tile 1 may be pending), and every wave has read its queries
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
-  if (ntiles > 0) issue_first(2);
+  if (ntiles > 1) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
+    issue_first(2);
+  } else {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
   fetch_next(kStages - 1);
   if (ntiles > 0) {
     const int e_tile = (L - kv_lo + kBK - 1) / kBK - 1;   // the tile holding key L - 1
@@ -1029,11 +1042,28 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
   const float lse = lt > 0.f ? m_run + __log2f(lt) : -INFINITY;
 #pragma unroll
   for (int md = 0; md < DM; ++md) o[md] *= inv;
+  if (w.slot < 0 && ncols - w.col_start <= kCols / 2) {
+    // half of the tile or less (no second group): straight from registers, 34 prompts of 21 tokens
+    // 15.2 us against 15.9 through LDS; on full tiles the same stores took 4 us per item
+    if (!cval) return;
+    uint16_t* dst = out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + col % G) * D;
+#pragma unroll
+    for (int md = 0; md < DM; ++md)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4_t v;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
+        *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * hg) = __builtin_convertvector(v, bf16x4_t);
+      }
+    return;
+  }
   if (w.slot < 0) {
     // Through LDS ([column][dim], this wave's own rows), so that rows leave as whole 16-byte
-    // chunks: 8-byte stores of lanes a row apart took 4 us per item.
+    // chunks.
     constexpr int EP = 2 * D + 16;                     // row pitch in bytes
     asm volatile("s_barrier" ::: "memory");            // no wave reads the ring any more
+    if (w.col_start + wave * 32 >= ncols) return;
     char* ep = smem + wave * (32 * EP);
 #pragma unroll
     for (int md = 0; md < DM; ++md)
@@ -1054,20 +1084,34 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 1) void prefill_attn_pp_kernel(
     }
     return;
   }
-  if (!cval) return;
   if (w.slot >= ws_slots) return;
-  const int local = wave * 32 + l32;
-  float* po = ws_o + (static_cast<int64_t>(w.slot) * kCols + local) * D;
+  // Partials: the same way, half of the dims (rows of 2 D bytes) at a time.
+  constexpr int EP = 2 * D + 16;
+  asm volatile("s_barrier" ::: "memory");
+  if (w.col_start + wave * 32 >= ncols) return;
+  char* ep = smem + wave * (32 * EP);
+  float* po = ws_o + (static_cast<int64_t>(w.slot) * kCols + wave * 32) * D;
 #pragma unroll
-  for (int md = 0; md < DM; ++md)
+  for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      f32x4_t v;
+    for (int m = 0; m < DM / 2; ++m)
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
-      *reinterpret_cast<f32x4_t*>(po + md * 32 + 8 * r4 + 4 * hg) = v;
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4_t v;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) v[jj] = o[half * (DM / 2) + m][4 * r4 + jj];
+        *reinterpret_cast<f32x4_t*>(ep + l32 * EP + (m * 32 + 8 * r4 + 4 * hg) * 4) = v;
+      }
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+      const int r = i * QROWS + lane / (D / 8), ch = lane % (D / 8);
+      const int c = w.col_start + wave * 32 + r;
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ep + r * EP + ch * 16);
+      if (c < ncols && (q0 + c / G) < n_q)
+        *reinterpret_cast<f32x4_t*>(po + static_cast<int64_t>(r) * D + half * (D / 2) + ch * 4) = v;
     }
-  if (hg == 0) ws_lse[static_cast<int64_t>(w.slot) * kCols + local] = lse;
+  }
+  if (cval && hg == 0) ws_lse[static_cast<int64_t>(w.slot) * kCols + wave * 32 + l32] = lse;
 }
 
 // Merges the key-range splits of one query tile: o = sum_s 2^(lse_s - M) O_s / sum_s 2^(lse_s - M)
@@ -1190,6 +1234,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   }
 }
 
+constexpr int64_t kUnits = 256;  // compute units of an MI355X
 constexpr int kWideNB = 1;  // 32-column MFMA blocks per wave on wide tiles
 constexpr int kWideWaves = arckv::kWideCols / (32 * kWideNB);
 static_assert(kWideWaves * 32 * kWideNB == arckv::kWideCols, "wide tile width");
@@ -1254,8 +1299,12 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
     const dim3 list_grid(static_cast<unsigned>(n_work / arckv::kListItems));
 #define ARCKV_LAUNCH(DD, GG)                                                                   \
   do {                                                                                         \
-    if (tile_cols == arckv::kWideCols)                                                         \
-      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG>), grid, dim3(512), 0, st, kp, vp, qp, op, \
+    if (tile_cols == arckv::kWideCols && DD == 64 && n_work > kUnits)                          \
+      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, DD == 64>), grid, dim3(512), 0, st, kp, vp, qp, op, \
+                         block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
+                         num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
+    else if (tile_cols == arckv::kWideCols)                                                    \
+      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
     else                                                                                       \
