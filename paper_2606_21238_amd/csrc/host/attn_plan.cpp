@@ -9,7 +9,9 @@
 // fewer empty columns.  When a batch has fewer tiles than compute units (short suffixes over long cached
 // prefixes), tiles are split along the key range so that the whole batch runs as one round of
 // at most one item per compute unit: the smallest cap on key tiles per item (at least 8, i.e.
-// 512 keys) for which the pieces fit, each tile cut into equal pieces under the cap.  Split
+// 512 keys) for which the pieces fit, each tile cut into equal pieces under the cap; or, where
+// equal pieces would leave many units idle, into pieces of one length and a remainder, the
+// remainders sharing the units that are left.  Split
 // items write fp32 partials plus a base-2 log-sum-exp, merged afterwards by one combine item
 // per tile.
 //
@@ -42,9 +44,29 @@ namespace {
 
 constexpr int kKeyTile = 64;  // keys per K/V tile (split boundaries are multiples of this)
 constexpr int kXcds = 8;      // MI355X: 8 XCDs; dispatch round-robins work-groups over them
+constexpr int kEngines = 4;   // shader engines of an XCD
 constexpr int64_t kItemCost = 4;  // list plans: cost of one item beyond its key tiles (measured)
 constexpr int64_t kMinPiece = 4;  // list plans: shortest piece a cut may leave, in key tiles
 constexpr int64_t kXcdSkewPermille = 25;  // work shifted from odd to even XCDs, per mille (measured)
+
+// Uneven wide plans, times in key tiles of a wide tile (1.4 us): what an item costs beside its
+// key tiles (8 us measured); pieces whose partial results are written and read back per key tile
+// (384 pieces, 50 MB: 17 us in the attention kernel, 14 in the combine) and the combine's launch; and
+// the time, in per cent of the equal cut's, up to which the uneven cut is taken.  Measured, equal
+// and uneven cut, with the time estimated for the second in per cent of the first's: 600 tokens
+// on 32768 cached, 64 / 8 heads, 71 %: 745 and 560 us; 4 turns of 300 on 20000, 32 / 8, 74 %: 463 and
+// 378; 8 questions of 128 on 8192, 40 / 8, 95 %: 199 and 197; 5 of 200 on 4000, 100 %: 100 and 102.
+constexpr int64_t kWideItemCost = 5;
+constexpr int64_t kSlotsPerKeyTile = 18;
+constexpr int64_t kCombineCost = 2;
+constexpr int64_t kWideGainPercent = 90;
+
+// pieces of a tile of nt key tiles cut into pieces of F and a remainder; a remainder under
+// kMinPiece joins the piece before it
+int64_t uneven_pieces(int64_t nt, int64_t F) {
+  const int64_t k = nt / F, r = nt - k * F;
+  return std::max<int64_t>(1, k + (r >= kMinPiece || (k == 0 && r > 0) ? 1 : 0));
+}
 
 struct Item {
   int32_t v[ARCKV_WORK_INTS];
@@ -197,6 +219,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
   }
 
   int64_t cap = INT32_MAX;  // key tiles per item
+  bool uneven = false;      // pieces of cap key tiles and a remainder, instead of equal pieces
   if (base > 0) {
     int64_t total_t = 0, max_t = 0;
     for (const Tile& t : tiles) {
@@ -217,21 +240,77 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
       cap = share;  // several rounds: no item longer than one compute unit's share
     }
     cap = std::min<int64_t>(cap, arckv::kMaxItemKeys / kKeyTile);
+    if (base < target && target >= kXcds) {
+      // Equal pieces leave compute units idle where the tiles are more than half of them (192
+      // tiles on 256 units cannot be cut at all).  Instead, every tile can be cut into pieces of
+      // F key tiles, one per unit, and a remainder, several of which share a unit: the smallest F
+      // for which they fit (as many to a unit as the longest allows).  The launch then takes about
+      // F + kWideItemCost key tiles of time, plus the partial results' way through memory; it has
+      // to be worth it.
+      // (every query tile comes once per KV head: the tiles' lengths are counted in such runs)
+      std::vector<int64_t> lengths;
+      for (size_t i = 0; i < tiles.size(); i += num_kv_heads) lengths.push_back(key_tiles(tiles[i]));
+      int64_t equal_slots = 0;
+      for (const int64_t nt : lengths) {
+        const int64_t n = (nt + cap - 1) / cap;
+        equal_slots += n > 1 ? n * num_kv_heads : 0;
+      }
+      const int64_t before =
+          cap + kWideItemCost + (equal_slots > 0 ? equal_slots / kSlotsPerKeyTile + kCombineCost : 0);
+      int64_t slots = 0;  // of the cut that `fits` looked at last
+      auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+      int64_t n_groups = 0;
+      for (int32_t r = 0; r < n_reqs; ++r) n_groups += cu_q[r + 1] > cu_q[r] ? num_kv_heads : 0;
+      // share of the items on one XCD (spread over all of them when the groups are fewer)
+      const int64_t on_one = n_groups >= kXcds ? up(n_groups, kXcds) : 1;
+      if (n_groups < kXcds) n_groups = kXcds;
+      const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
+      auto fits = [&](int64_t F) {
+        int64_t full = 0, rests = 0, longest = 0;
+        slots = 0;
+        for (const int64_t nt : lengths) {
+          const int64_t k = uneven_pieces(nt, F), r = nt - (k - 1) * F;
+          full += (k - 1 + (r >= F)) * num_kv_heads;
+          rests += r < F ? num_kv_heads : 0;
+          longest = r < F ? std::max(longest, r) : longest;
+          slots += k > 1 ? k * num_kv_heads : 0;
+        }
+        const int64_t per_unit = (F + kWideItemCost) / (longest + kWideItemCost);  // >= 1
+        // counted for the fullest group of units that the dispatcher fills by turns: whole
+        // (request, KV head) groups go to one XCD, and its work-groups to its shader engines in
+        // order, whichever of them has a free unit (22 groups: a fourth of an XCD got 6 pieces
+        // and 5 remainders for its 8 units, and the launch took 281 us where 200 were planned)
+        return up(up(full * on_one, n_groups), engines) + up(up(up(rests * on_one, n_groups), engines), per_unit) <=
+               target / (kXcds * engines);
+      };
+      int64_t lo = share, hi = (share + kWideItemCost + kCombineCost) * 100 <= before * kWideGainPercent ? cap : lo;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (fits(mid)) hi = mid; else lo = mid + 1;
+      }
+      const int64_t slot_bytes = kCols * (static_cast<int64_t>(head_dim) + 1) * 4;
+      uneven = lo + kMinPiece <= arckv::kMaxItemKeys / kKeyTile && fits(lo) &&
+               (lo + kWideItemCost + slots / kSlotsPerKeyTile + kCombineCost) * 100 <= before * kWideGainPercent &&
+               slots * slot_bytes <= ARCKV_NOALLOC_MAX_WS_BYTES;
+      if (uneven) cap = lo;
+    }
   }
 
   std::vector<Item> items, combines;
   int64_t slot = 0;
   for (const Tile& t : tiles) {
     const int64_t nt = key_tiles(t);
-    const int64_t ns = (nt + cap - 1) / cap;
+    const int64_t ns = uneven ? uneven_pieces(nt, cap) : (nt + cap - 1) / cap;
     const int64_t group = static_cast<int64_t>(t.req) * num_kv_heads + t.kvh;
     if (ns <= 1) {
       items.push_back({{t.req, t.kvh, t.col_start, 0, t.kv_end, -1, 0, 0}, t.kv_end, group});
       continue;
     }
-    for (int64_t s = 0; s < ns; ++s) {  // equal pieces of whole key tiles
-      const int32_t a = static_cast<int32_t>(s * nt / ns * kKeyTile);
-      const int32_t b = static_cast<int32_t>(std::min<int64_t>((s + 1) * nt / ns * kKeyTile, t.kv_end));
+    for (int64_t s = 0; s < ns; ++s) {  // pieces of whole key tiles
+      const int64_t a_t = uneven ? s * cap : s * nt / ns;
+      const int64_t b_t = uneven ? (s + 1 < ns ? (s + 1) * cap : nt) : (s + 1) * nt / ns;
+      const int32_t a = static_cast<int32_t>(a_t * kKeyTile);
+      const int32_t b = static_cast<int32_t>(std::min<int64_t>(b_t * kKeyTile, t.kv_end));
       items.push_back({{t.req, t.kvh, t.col_start, a, b, static_cast<int32_t>(slot + s), 0, 0}, b - a, group});
     }
     combines.push_back({{t.req, t.kvh, t.col_start, static_cast<int32_t>(slot), static_cast<int32_t>(ns), 0, 0, 0}, 0, group});

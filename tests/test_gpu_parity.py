@@ -198,6 +198,27 @@ def test_attention_sweep(case, num_cus):
         assert (ap.work[: ap.n_work, 5] >= 0).any()
 
 
+# Plans whose tiles are cut into pieces of one length and a remainder (more than half as many
+# tiles as compute units): partial results of both lengths, ragged last pieces and columns.
+UNEVEN = [
+    ([(2000, 1800)], 16, 8, 128, 24),
+    ([(1990, 1783)], 16, 8, 64, 24),
+    ([(2500, 2397)], 40, 8, 128, 40),
+]
+
+
+@pytest.mark.parametrize("reqs,hq,hkv,d,num_cus", UNEVEN)
+def test_attention_uneven_pieces(reqs, hq, hkv, d, num_cus):
+    print_case(f"uneven pieces {reqs} hq={hq} hkv={hkv} d={d} num_cus={num_cus}")
+    b = build_batch(reqs, hq, hkv, d, seed=77 + d)
+    got, ap = run_attention(b, hq, hkv, d, num_cus)
+    w = ap.work[: ap.n_work]
+    first = w[(w[:, 5] >= 0) & (w[:, 3] == 0)]
+    rest = w[(w[:, 5] >= 0) & (w[:, 3] > 0)]
+    assert len(first) and (rest[:, 4] - rest[:, 3]).max() < (first[:, 4] - first[:, 3]).min() - 64
+    compare(got, oracle_out(b, hq, hkv, d), "uneven pieces")
+
+
 # Scores that grow, jump or spike along the keys, so that the running maximum moves after the
 # first key tile of an item (the online softmax's rescale), and scores that fall (it never
 # does).  With N(0, 1) inputs a 128-dim score has a standard deviation of about 1.4 in log2

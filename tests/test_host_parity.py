@@ -361,6 +361,47 @@ def test_attention_plan_covers_every_tile_once():
     attention_plan_coverage([0, 51, 103], [4000, 103], 40, 8, 128, 256)
 
 
+def test_attention_plan_uneven_pieces():
+    """More than half as many wide tiles as compute units: pieces of one length F and a remainder,
+    where that shortens the launch; every key covered once, no piece under 4 key tiles, consecutive
+    slots, the workspace within the static scratch; and the equal cut where nothing is gained."""
+    taken = 0
+    for S, L, hq, hkv, cus in (([128] * 8, [8320] * 8, 40, 8, 256), ([300] * 4, [20300] * 4, 32, 8, 256),
+                               ([200], [2000], 16, 8, 24), ([103, 100], [2500, 700], 40, 8, 64),
+                               ([600], [33368], 64, 8, 256), ([900], [20900], 40, 8, 256), ([256] * 7, [1256] * 7, 32, 8, 256),
+                               ([600] * 3, [70000] * 3, 32, 8, 256), ([64], [320], 4, 2, 256)):
+        cu = np.concatenate([[0], np.cumsum(S)]).astype(np.int32)
+        ap = ak.attention_plan(cu, L, hq, hkv, 128, cus)
+        assert ap.tile_cols == 256 or max(S) * hq // hkv <= 128
+        if ap.tile_cols != 256:
+            continue
+        g, w, comb = hq // hkv, ap.work[: ap.n_work], ap.work[ap.n_work: ap.n_work + ap.n_combine]
+        sizes, n_slots = [], 0
+        for r in range(len(S)):
+            for cs in range(0, S[r] * g, 256):
+                kv_end = L[r] - S[r] + (min(cs + 256, S[r] * g) - 1) // g + 1
+                for h in range(hkv):
+                    p = w[(w[:, 0] == r) & (w[:, 1] == h) & (w[:, 2] == cs)]
+                    p = p[np.argsort(p[:, 3])]
+                    assert p[0, 3] == 0 and p[-1, 4] == kv_end and (p[1:, 3] == p[:-1, 4]).all()
+                    if len(p) == 1:
+                        assert p[0, 5] == -1
+                        continue
+                    n = (p[:, 4] - p[:, 3] + 63) // 64
+                    sizes.append(n)
+                    assert (p[:, 3] % 64 == 0).all() and n.min() >= 4 and n.max() <= 1024
+                    assert (np.diff(p[:, 5]) == 1).all()
+                    assert any(list(c[:5]) == [r, h, cs, p[0, 5], len(p)] for c in comb)
+                    n_slots += len(p)
+        assert (w[:, 0] >= 0).sum() == n_slots + sum(hkv * -(-s * g // 256) for s in S) - len(sizes)
+        assert ap.ws_bytes == n_slots * 256 * 129 * 4 and ap.ws_bytes <= ak.NOALLOC_MAX_WS_BYTES
+        if any(n.max() - n.min() > 1 for n in sizes):
+            taken += 1
+            full = {int(n[0]) for n in sizes}
+            assert max(full) - min(full) < 4       # one length F (a short remainder joins its piece)
+    assert taken >= 4       # and the equal cut elsewhere
+
+
 def test_list_plans_cover_and_balance():
     """Narrow batches (at most 128 columns per request): per-work-group lists of 8 entries,
     about equal cost per list, no cut piece under 4 key tiles."""
