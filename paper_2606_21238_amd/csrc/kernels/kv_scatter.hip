@@ -11,11 +11,20 @@
 // otherwise.  K rows are copied as 16-byte chunks.  V rows are staged through LDS and written
 // dim-major.  A run is 8 tokens of the work-group whose slots are 8 consecutive slots of one
 // block starting at a multiple of 8 (most of a prefill, wherever its request starts in the
-// batch); a run's 8 values of one dimension go out as one 16-byte store, with consecutive
-// lanes on consecutive dimensions so that a wave's stores are contiguous.  Every other token
-// is written the coalesced 2-byte way: lane = token, 64 consecutive tokens of one dimension
-// per store instruction.  Bytes are copied, never converted: the result is bit-exact.  Slots
-// outside the pool are skipped.
+// batch); a run's 8 values of one dimension go out as one 16-byte store, neighbouring lanes on
+// the two runs of one block and then on consecutive dimensions, so that a wave's stores fill
+// whole lines.  Every other token is written the coalesced 2-byte way: lane = token, 64
+// consecutive tokens of one dimension per store instruction.  Bytes are copied, never converted:
+// the result is bit-exact.  Slots outside the pool are skipped.
+//
+// What bounds it is memory, and the chain slots -> barrier -> load -> store before it was cut: the
+// rows do not depend on the slots, so a thread asks for all of its chunks first.  The rows are
+// read once and non-temporally, which leaves the caches to the pools that attention reads next.
+// 24898 tokens of 8 heads of 128 (204 MB): 47.0 us, 42.4 with the early loads and the paired runs,
+// 40.3 with non-temporal loads too (5.1 TB/s, a large copy reaches 5.0), and a pass over the pool
+// right after it 34.9, 36.6 and 30.8 us.  13390 tokens of 16 heads of 64: 26.2, 24.4, 20.6.
+// (Non-temporal stores as well: 38.2 us, but slots that straddle the work-groups' 64 tokens 46.7
+// against 45.4 and head_dim 64 21.3 with a slower pass after it.)
 #include <hip/hip_runtime.h>
 
 #include "../host/internal.hpp"
@@ -26,6 +35,12 @@ namespace {
 constexpr int kTok = 64;              // tokens per work-group: one wave's lanes
 constexpr int kThreads = 256;
 constexpr int kMaxRuns = kTok / 8;
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ u32x4_t load_once(const uint16_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+}
 
 template <int D, int DPW>
 __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
@@ -44,6 +59,20 @@ __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
   const int d0 = blockIdx.z * DPW;     // first dimension of the slice
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTok;
   const int tid = threadIdx.x;
+  // this thread's chunks of the rows (those past the last token repeat its row and are not used)
+  constexpr int kChunks = kTok * CH;
+  constexpr int N = (kChunks + kThreads - 1) / kThreads;
+  u32x4_t kv[N], vv[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int c = tid + i * kThreads;
+    if (c < kChunks) {
+      const int64_t t = min(t0 + c / CH, n_tokens - 1);
+      const int64_t src = (t * hkv + h) * D + d0 + (c % CH) * 8;
+      kv[i] = load_once(k_new + src);
+      vv[i] = load_once(v_new + src);
+    }
+  }
   if (tid < kTok) {
     const int64_t t = t0 + tid;
     const int32_t s = t < n_tokens ? slots[t] : -1;
@@ -68,27 +97,33 @@ __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
       n_runs = __builtin_popcountll(m);
     }
   }
-  // K: direct 16-byte copies; V: into LDS (row = token, padded)
-  for (int c = tid; c < kTok * CH; c += kThreads) {
-    const int tl = c / CH, ch = c % CH;
-    const int64_t t = t0 + tl;
-    if (t >= n_tokens) continue;
-    const int64_t src = (t * hkv + h) * D + d0 + ch * 8;
-    const int32_t s = sslot[tl];
-    if (s >= 0) {
-      const uint4 kv = *reinterpret_cast<const uint4*>(k_new + src);
-      const int64_t blk = s >> 4;
-      *reinterpret_cast<uint4*>(k_pool + ((blk * hkv + h) * 16 + (s & 15)) * D + d0 + ch * 8) = kv;
+  // V into LDS (row = token, padded), K straight to its slots
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int c = tid + i * kThreads, tl = c / CH, ch = c % CH;
+    if (c < kChunks) {
+      uint32_t* dst = sv32 + (tl * VROW + ch * 8) / 2;  // VROW and ch*8 are even: 4-byte aligned
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dst[j] = vv[i][j];
     }
-    const uint4 vv = *reinterpret_cast<const uint4*>(v_new + src);
-    uint32_t* dst = sv32 + (tl * VROW + ch * 8) / 2;  // VROW and ch*8 are even: 4-byte aligned
-    dst[0] = vv.x; dst[1] = vv.y; dst[2] = vv.z; dst[3] = vv.w;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int c = tid + i * kThreads, tl = c / CH, ch = c % CH;
+    if (c < kChunks) {
+      const int32_t s = sslot[tl];                      // -1 past the last token
+      if (s >= 0)
+        *reinterpret_cast<u32x4_t*>(k_pool + ((static_cast<int64_t>(s >> 4) * hkv + h) * 16 + (s & 15)) * D + d0 + ch * 8) = kv[i];
+    }
   }
   __syncthreads();
-  // V of the runs: (run, dimension) per thread, dimensions fastest across lanes
+  // V of the runs: (pair of runs, dimension, run of the pair) per thread; where the first run is
+  // the upper half of a block, the pairs start one run earlier
   const int nr = n_runs;
-  for (int e = tid; e < nr * DPW; e += kThreads) {
-    const int r = e / DPW, dl = e % DPW, d = d0 + dl;
+  const int odd = nr > 0 ? (run_slot[0] >> 3) & 1 : 0;
+  for (int e = tid; e < (nr + odd + 1) / 2 * (2 * DPW); e += kThreads) {
+    const int r = e / (2 * DPW) * 2 + (e & 1) - odd, dl = (e >> 1) % DPW, d = d0 + dl;
+    if (r < 0 || r >= nr) continue;
     const int tl = run_tok[r];
     const int32_t sb = run_slot[r];
     uint16_t v8[8];
