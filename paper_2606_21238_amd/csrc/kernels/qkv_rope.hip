@@ -202,14 +202,16 @@ __device__ __forceinline__ void store_tile(const char* ep, int pitch, int t0, in
 // tile writes took every LDS cycle the MFMAs left); with one wave per SIMD the accumulators
 // (256 registers) and two sets of operands fit, so a step's MFMAs run with the next step's
 // operand reads and the loads between them, one barrier per 64 columns.  x tiles have a ring
-// of three stages and W tiles of two (160 KiB in all): stage s + 2 is requested while stage s
-// is multiplied.
+// of three stages; W tiles of WS = 2 at TM = 256 (160 KiB in all), where a stage takes as long as
+// a load, and of 3 at TM = 128 (144 KiB): its stages are half as long, and W requested 3/4 of a
+// stage ahead bound them (907 tokens x 5120 x 7168: 91.7 us with 2, 80.7 with 3; 512 x 8192 x
+// 10240: 129 and 112).
 //
 // Stage s, four steps of 16 columns (the operands of a step are read during the step before):
 //   step 0       requests x(s + 2), into the buffer of x(s - 1)
 //   after step 2 this wave's reads of stage s have returned and its loads of stage s + 1 are
-//                complete (x(s + 2) may be pending); barrier
-//   step 3       requests W(s + 2), into the buffer of W(s); reads step 0 of stage s + 1
+//                complete (x(s + 2), and W(s + 2) with WS = 3, may be pending); barrier
+//   step 3       requests W(s + WS), into the buffer of W(s); reads step 0 of stage s + 1
 // Stages past the end are requested as copies of the last one, into buffers nobody reads any
 // more, which keeps the counts constant.
 //
@@ -228,7 +230,8 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
   constexpr int XB = TM * kKC * 2, WB = kTN * kKC * 2;  // bytes of an x and of a W stage
   constexpr int XL = TM / 32, WL = kTN / 32;            // 1 KiB loads per wave of each (8 rows)
   constexpr int kPitch = kTN * 2 + 16;
-  constexpr int kRing = 3 * XB + 2 * WB, kEnd = TM * kPitch + TM * 4;
+  constexpr int WS = MB == 2 ? 3 : 2;                   // stages of the W ring
+  constexpr int kRing = 3 * XB + WS * WB, kEnd = TM * kPitch + TM * 4;
   __shared__ __attribute__((aligned(1024))) char smem[kRing > kEnd ? kRing : kEnd];  // rings, then y and slots
   // Tile order.  Work-groups are dealt to the 8 XCDs in turn (b -> XCD b % 8) and each XCD has
   // its own L2, so logical tile L = (b % 8) * (G / 8) + b / 8 gives every XCD a contiguous run
@@ -273,10 +276,10 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
     const int sc = min(s, n_st - 1);
     load_lds16(xbase + sc * kKC, xofs[i] - back(sc), (lds_void*)(smem + buf * XB + (32 * i + 8 * wave) * 128));
   };
-  auto issue_w = [&](int s, int i) __attribute__((always_inline)) {
+  auto issue_w = [&](int s, int buf, int i) __attribute__((always_inline)) {
     const int sc = min(s, n_st - 1);
     load_lds16(wbase + sc * kKC, wofs[i] - back(sc),
-               (lds_void*)(smem + 3 * XB + (s & 1) * WB + (32 * i + 8 * wave) * 128));
+               (lds_void*)(smem + 3 * XB + buf * WB + (32 * i + 8 * wave) * 128));
   };
 
   f32x16_t acc[MB][4];
@@ -316,38 +319,41 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
     }
   };
 #pragma unroll
-  for (int i = 0; i < WL; ++i) issue_w(0, i);
+  for (int i = 0; i < WL; ++i) issue_w(0, 0, i);
 #pragma unroll
   for (int i = 0; i < XL; ++i) issue_x(0, 0, i);
 #pragma unroll
   for (int i = 0; i < XL; ++i) issue_x(1, 1, i);
 #pragma unroll
-  for (int i = 0; i < WL; ++i) issue_w(1, i);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XL + WL) : "memory");
+  for (int k = 1; k < WS; ++k)
+#pragma unroll
+    for (int i = 0; i < WL; ++i) issue_w(k, k, i);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XL + (WS - 1) * WL) : "memory");
 #pragma unroll
   for (int i = 0; i < NOP; ++i) op[0][i] = rd(0, 0, 0, i);
   int x3 = 0;                                           // s % 3
   for (int s = 0; s < n_full; ++s) {
-    const int xo = x3 * XB, wo = (s & 1) * WB;
     const int xn = x3 == 2 ? 0 : x3 + 1;
+    const int wb = WS == 3 ? x3 : s & 1;
+    const int xo = x3 * XB, wo = wb * WB, wn = (WS == 3 ? xn : wb ^ 1) * WB;
     auto no_load = [](int) {};
     step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 1, i); },
          [&](int i) __attribute__((always_inline)) { if (i < XL) issue_x(s + 2, x3 == 0 ? 2 : x3 - 1, i); });
     if constexpr (XL > 2 * MB) static_assert(XL <= 2 * MB, "every x load has its place in the step");
     step(1, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 2, i); }, no_load);
     step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 3, i); }, no_load);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XL) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XL + (WS - 2) * WL) : "memory");
     __builtin_amdgcn_sched_barrier(0);
-    step(1, [&](int i) __attribute__((always_inline)) { return rd(xn * XB, WB - wo, 0, i); },
+    step(1, [&](int i) __attribute__((always_inline)) { return rd(xn * XB, wn, 0, i); },
          [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-           for (int k = 0; k < WL / (2 * MB); ++k) issue_w(s + 2, i * (WL / (2 * MB)) + k);
+           for (int k = 0; k < WL / (2 * MB); ++k) issue_w(s + WS, wb, i * (WL / (2 * MB)) + k);
          });
     __builtin_amdgcn_sched_barrier(0);
     x3 = xn;
   }
   if (n_st > n_full) {                                  // 32 columns left: two steps
-    const int xo = x3 * XB, wo = (n_full & 1) * WB;
+    const int xo = x3 * XB, wo = (WS == 3 ? x3 : n_full & 1) * WB;
     step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 1, i); }, [](int) {});
     step(1, [&](int i) __attribute__((always_inline)) { return op[0][i]; }, [](int) {});
   }
@@ -605,9 +611,10 @@ namespace {
 //             long enough to outweigh their reduction (T = 256: 30.7, hidden 5120: 38.7 against
 //             46.9 with 64 x 32; before 97 and 137), else 64 x 32 (hidden 1024, 3072 outputs,
 //             T = 256: 10.2 against 13.5).  Past that the prefill kernel's reuse wins: hidden 8192,
-//             T = 512 (5 tiles per unit): 129 against 149; hidden 5120, T = 512 (3.5): 83 against 77
-//   prefill   128-token tiles when they need fewer rounds of the chip for their 0.6 of a 256-token
-//             tile's time: hidden 5120, T = 907: 89 against 117; T = 2000: 173 against 136
+//             T = 512 (5 tiles per unit): 112 against 149; hidden 5120, T = 450 (3.5): 78 against 76
+//   prefill   128-token tiles when they need fewer rounds of the chip for their 0.6 to 0.7 of a
+//             256-token tile's time: hidden 5120, T = 907: 81 against 119 (one round each); T = 3000
+//             (3 and 2 rounds): 222 against 233; T = 2000 (2 and 1): 158 against 132
 enum class QkvRoute { kK32x32Wide, kK32x32, kK64x32, kK64x64, kG128, kG256 };
 constexpr int64_t kUnits = 256;   // compute units of an MI355X
 QkvRoute qkv_route(int64_t n_tokens, int64_t hidden, int64_t n_out) {

@@ -214,6 +214,7 @@ ROUTES = [
     ("64x64 tiles", [(40, 3), (900, 850)], 2080, 32, 8, 128),
     ("64x64 tiles, d 64", [(129, 0)], 2112, 96, 48, 64),
     ("128-token tiles, ragged", [(2390, 0)], 96, 8, 2, 128),
+    ("128-token tiles, the rings go round", [(2390, 7)], 416, 8, 2, 128),
     ("128-token tiles, d 64, half an output tile", [(2301, 1), (257, 100)], 64, 22, 2, 64),
     ("256-token tiles, ragged", [(6001, 0), (500, 170)], 160, 8, 2, 128),
     ("256-token tiles, d 64, one stage", [(6000, 0), (331, 1)], 32, 20, 2, 64),
