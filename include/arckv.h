@@ -317,7 +317,8 @@ int32_t arckv_kv_scatter(void* k_pool, void* v_pool, const void* k_new, const vo
 /* Work decomposition (host): one work item is a query tile of *tile_cols (column = token x
  * query head of one KV group, token-major) of one (request, KV head) over a key range.
  * 256-column tiles: one work-group per item; long key ranges are split when the batch has too
- * few tiles to fill num_cus compute units (into one round of at most num_cus items).
+ * few tiles to fill num_cus compute units (into one round of at most num_cus items, or of num_cus
+ * units' worth of items where shorter ones share a unit).
  * 128-column tiles: the items are grouped into lists of 8 entries (the list's items, then idle
  * entries with request -1), one list per work-group, balanced over at most num_cus lists;
  * key ranges are cut where a list's share ends.  Split tiles are merged by a log-sum-exp
@@ -445,8 +446,8 @@ int32_t arckv_prefill_attention_noalloc(const void* k_pool, const void* v_pool, 
  * pairs of every token as fp32), caller-owned.  q_out: device bf16 [n_tokens][num_q_heads]
  * [head_dim]; k_out, v_out: device bf16 [n_tokens][num_kv_heads][head_dim] (the layout
  * arckv_kv_scatter takes).  x, w_qkv, workspace, q_out, k_out and v_out must be 16-byte
- * aligned.  One fused kernel (GEMM tile + rotation in its epilogue) after a small table
- * pass; y never goes to memory.  Stream-ordered on `stream`.  head_dim in {64, 128}, hidden a
+ * aligned.  One fused kernel (GEMM tile + rotation in its epilogue), for prefill batches after a
+ * small table pass into the workspace; y never goes to memory.  Stream-ordered on `stream`.  head_dim in {64, 128}, hidden a
  * multiple of 32 (at most 2^22) and (num_q_heads + 2 num_kv_heads) head_dim a multiple of 128: else
  * EUNSUPPORTED; EINVAL on bad sizes, NULL or misaligned pointers or rope_theta <= 1; ENOSPC if
  * the workspace is too small; EDEVICE if a launch fails.  n_tokens = 0 is a no-op. */
