@@ -642,7 +642,9 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // item's prologue runs beside the other's steps: 12 uncached prompts of 1100 tokens 78 -> 68 us.
 // PAIRED is that build (128 registers).  With no more items than units it would let the dispatcher
 // put two on one unit and leave another idle (3 turns on 2000 cached tokens: 57 us against 49).
-template <int D, int G, bool PAIRED>
+// ANY takes queries and outputs that are not 16-byte aligned (a caller's view), through registers;
+// as a branch in the aligned build it cost the 16 conversation turns 3 %, all that the prologue gained.
+template <int D, int G, bool PAIRED, bool ANY>
 __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
     const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
@@ -968,7 +970,14 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
       const int c = w.col_start + wave * 32 + r;       // columns past the request load row 0, never used
       const bool ok = c < ncols && (q0 + c / G) < n_q;
       const int64_t row = ok ? static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G : 0;
-      load_lds16(q + row * D + (((lane % (D / 8)) ^ fk<D>(r)) * 8), (lds_void*)(qst + i * 1024));
+      const uint16_t* src = q + row * D + (((lane % (D / 8)) ^ fk<D>(r)) * 8);
+      if constexpr (!ANY) {
+        load_lds16(src, (lds_void*)(qst + i * 1024));
+      } else {
+        u32x4_t v;
+        __builtin_memcpy(&v, src, 16);
+        *reinterpret_cast<u32x4_t*>(qst + i * 1024 + lane * 16) = v;
+      }
     }
     issue_first(0);
     // With a second tile, tiles 1 and 2 always go out (2 past the key range: block 0 into a stage
@@ -1080,7 +1089,11 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
       const int c = w.col_start + wave * 32 + r;
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(ep + r * EP + ch * 16);
       if (c < ncols && (q0 + c / G) < n_q)
-        *reinterpret_cast<u32x4_t*>(out + (static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G) * D + ch * 8) = v;
+      {
+        uint16_t* dst = out + (static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G) * D + ch * 8;
+        if constexpr (ANY) __builtin_memcpy(dst, &v, 16);
+        else *reinterpret_cast<u32x4_t*>(dst) = v;
+      }
     }
     return;
   }
@@ -1296,15 +1309,20 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
   if (!record(ev_begin)) return arckv::fail(ARCKV_EDEVICE, "prefill_attention: event record failed");
   if (n_work > 0) {
     const dim3 grid(static_cast<unsigned>(n_work));
+    const bool any_align = (reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(out)) % 16 != 0;
     const dim3 list_grid(static_cast<unsigned>(n_work / arckv::kListItems));
 #define ARCKV_LAUNCH(DD, GG)                                                                   \
   do {                                                                                         \
-    if (tile_cols == arckv::kWideCols && DD == 64 && n_work > kUnits)                          \
-      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, DD == 64>), grid, dim3(512), 0, st, kp, vp, qp, op, \
+    if (tile_cols == arckv::kWideCols && any_align)                                            \
+      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false, true>), grid, dim3(512), 0, st, kp, vp, qp, op, \
+                         block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
+                         num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
+    else if (tile_cols == arckv::kWideCols && DD == 64 && n_work > kUnits)                     \
+      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, DD == 64, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
     else if (tile_cols == arckv::kWideCols)                                                    \
-      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
+      hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
     else                                                                                       \

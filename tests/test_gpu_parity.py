@@ -219,6 +219,31 @@ def test_attention_uneven_pieces(reqs, hq, hkv, d, num_cus):
     compare(got, oracle_out(b, hq, hkv, d), "uneven pieces")
 
 
+@pytest.mark.parametrize("d,hq,hkv,n", [(128, 8, 2, 1), (64, 16, 16, 9)])
+def test_wide_attention_of_views(d, hq, hkv, n):
+    """Query and output views that start 8 bytes into their storage: the same bits as aligned ones,
+    against both aligned builds of the wide kernel (n requests: fewer and more items than compute
+    units)."""
+    print_case(f"views d={d} hq={hq} hkv={hkv} n={n}")
+    from paper_2606_21238_amd.engine import PrefillEngine
+    rng = np.random.default_rng(d)
+    toks = [rng.integers(0, 1000, 555, dtype=np.int32) for _ in range(n)]
+    eng = PrefillEngine(hq, hkv, d, 40 * n, 41 * n, n, policy="arc", pool_fill=0)
+    db = eng.prepare(toks)
+    t = 555 * n
+    eng.scatter(db, randn_bf16((t, hkv, d), 1), randn_bf16((t, hkv, d), 2))
+    q = randn_bf16((t, hq, d), 3)
+    want = torch.empty_like(q)
+    eng.attention(db, q, want)
+    qv, ov = (torch.empty(q.numel() + 4, dtype=q.dtype, device=DEV)[4:].view(q.shape) for _ in range(2))
+    qv.copy_(q)
+    assert qv.data_ptr() % 16 == 8 and ov.data_ptr() % 16 == 8
+    eng.attention(db, qv, ov)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(ov), bits(want))
+    eng.release()
+
+
 # Scores that grow, jump or spike along the keys, so that the running maximum moves after the
 # first key tile of an item (the online softmax's rescale), and scores that fall (it never
 # does).  With N(0, 1) inputs a 128-dim score has a standard deviation of about 1.4 in log2
