@@ -402,6 +402,27 @@ def test_attention_plan_uneven_pieces():
     assert taken >= 4       # and the equal cut elsewhere
 
 
+@pytest.mark.parametrize("hkv", [1, 2, 4])
+def test_uneven_pieces_spread_over_xcds(hkv):
+    """Fewer (request, KV head) groups than XCDs: the long pieces of an uneven cut and its
+    remainders are both spread over the XCDs, a unit for every long piece."""
+    taken = 0
+    for S, L in ((1060, 10978), (1168, 21030), (1255, 16250), (2200, 12000), (2400, 21000), (4500, 20000)):
+        ap = ak.attention_plan(np.array([0, S], np.int32), [L], 8 * hkv, hkv, 128, 256)
+        w = ap.work[: ap.n_work]
+        n = np.where(w[:, 0] >= 0, (w[:, 4] - w[:, 3] + 63) // 64, 0)
+        first = n[(w[:, 5] >= 0) & (w[:, 3] == 0)]
+        F = int(np.median(first)) if len(first) else 0
+        if len(first) == 0 or n[w[:, 5] >= 0].min() > F - 4 or first.max() > F + 3 or first.min() < F:
+            continue                                    # the equal cut, or nothing cut
+        taken += 1
+        full = np.array([(n[x::8] >= F).sum() for x in range(8)])
+        rest = np.array([((n[x::8] > 0) & (n[x::8] < F)).sum() for x in range(8)])
+        assert full.max() - full.min() <= 1 and rest.max() - rest.min() <= 1, (full, rest)
+        assert full.max() <= 32
+    assert taken > 0
+
+
 def test_list_plans_cover_and_balance():
     """Narrow batches (at most 128 columns per request): per-work-group lists of 8 entries,
     about equal cost per list, no cut piece under 4 key tiles."""
