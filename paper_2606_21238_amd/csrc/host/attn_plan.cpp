@@ -52,8 +52,9 @@ constexpr int64_t kXcdSkewPermille = 25;  // work shifted from odd to even XCDs,
 // Uneven wide plans, times in key tiles of a wide tile (1.4 us): what an item costs beside its
 // key tiles (8 us measured); pieces whose partial results are written and read back per key tile
 // (384 pieces, 50 MB: 17 us in the attention kernel, 14 in the combine) and the combine's launch; and
-// the time, in per cent of the equal cut's, up to which the uneven cut is taken.  Measured, equal
-// and uneven cut, with the time estimated for the second in per cent of the first's: 600 tokens
+// the time, in per cent of the equal cut's, up to which the uneven cut is taken (both estimated on
+// the plans as they are dealt).  Measured, equal and uneven cut, with the time estimated for the
+// second in per cent of the first's: 600 tokens
 // on 32768 cached, 64 / 8 heads, 71 %: 745 and 560 us; 4 turns of 300 on 20000, 32 / 8, 74 %: 463 and
 // 378; 8 questions of 128 on 8192, 40 / 8, 95 %: 199 and 197; 5 of 200 on 4000, 100 %: 100 and 102.
 constexpr int64_t kWideItemCost = 5;
@@ -219,14 +220,14 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
   }
 
   int64_t cap = INT32_MAX;  // key tiles per item
-  bool uneven = false;      // pieces of cap key tiles and a remainder, instead of equal pieces
+  int64_t share = 0;        // of one compute unit, in key tiles
   if (base > 0) {
     int64_t total_t = 0, max_t = 0;
     for (const Tile& t : tiles) {
       total_t += key_tiles(t);
       max_t = std::max(max_t, key_tiles(t));
     }
-    const int64_t share = std::max<int64_t>(8, (total_t + target - 1) / target);
+    share = std::max<int64_t>(8, (total_t + target - 1) / target);
     if (base < target) {
       int64_t lo = share, hi = std::max(lo, max_t);
       while (lo < hi) {  // smallest cap whose pieces fit in one round
@@ -240,172 +241,196 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
       cap = share;  // several rounds: no item longer than one compute unit's share
     }
     cap = std::min<int64_t>(cap, arckv::kMaxItemKeys / kKeyTile);
-    if (base < target && target >= kXcds) {
-      // Equal pieces leave compute units idle where the tiles are more than half of them (192
-      // tiles on 256 units cannot be cut at all).  Instead, every tile can be cut into pieces of
-      // F key tiles, one per unit, and a remainder, several of which share a unit: the smallest F
-      // for which they fit (as many to a unit as the longest allows).  The launch then takes about
-      // F + kWideItemCost key tiles of time, plus the partial results' way through memory; it has
-      // to be worth it.
-      // (every query tile comes once per KV head: the tiles' lengths are counted in such runs)
-      std::vector<int64_t> lengths;
-      for (size_t i = 0; i < tiles.size(); i += num_kv_heads) lengths.push_back(key_tiles(tiles[i]));
-      int64_t equal_slots = 0;
-      for (const int64_t nt : lengths) {
-        const int64_t n = (nt + cap - 1) / cap;
-        equal_slots += n > 1 ? n * num_kv_heads : 0;
-      }
-      const int64_t before =
-          cap + kWideItemCost + (equal_slots > 0 ? equal_slots / kSlotsPerKeyTile + kCombineCost : 0);
-      int64_t slots = 0;  // of the cut that `fits` looked at last
-      auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-      int64_t n_groups = 0;
-      for (int32_t r = 0; r < n_reqs; ++r) n_groups += cu_q[r + 1] > cu_q[r] ? num_kv_heads : 0;
-      // share of the items on one XCD (spread over all of them when the groups are fewer)
-      const int64_t on_one = n_groups >= kXcds ? up(n_groups, kXcds) : 1;
-      if (n_groups < kXcds) n_groups = kXcds;
-      const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
-      auto fits = [&](int64_t F) {
-        int64_t full = 0, rests = 0, longest = 0;
-        slots = 0;
-        for (const int64_t nt : lengths) {
-          const int64_t k = uneven_pieces(nt, F), r = nt - (k - 1) * F;
-          full += (k - 1 + (r >= F)) * num_kv_heads;
-          rests += r < F ? num_kv_heads : 0;
-          longest = r < F ? std::max(longest, r) : longest;
-          slots += k > 1 ? k * num_kv_heads : 0;
-        }
-        const int64_t per_unit = (F + kWideItemCost) / (longest + kWideItemCost);  // >= 1
-        // counted for the fullest group of units that the dispatcher fills by turns: whole
-        // (request, KV head) groups go to one XCD, and its work-groups to its shader engines in
-        // order, whichever of them has a free unit (22 groups: a fourth of an XCD got 6 pieces
-        // and 5 remainders for its 8 units, and the launch took 281 us where 200 were planned)
-        return up(up(full * on_one, n_groups), engines) + up(up(up(rests * on_one, n_groups), engines), per_unit) <=
-               target / (kXcds * engines);
-      };
-      int64_t lo = share, hi = (share + kWideItemCost + kCombineCost) * 100 <= before * kWideGainPercent ? cap : lo;
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) / 2;
-        if (fits(mid)) hi = mid; else lo = mid + 1;
-      }
-      const int64_t slot_bytes = kCols * (static_cast<int64_t>(head_dim) + 1) * 4;
-      uneven = lo + kMinPiece <= arckv::kMaxItemKeys / kKeyTile && fits(lo) &&
-               (lo + kWideItemCost + slots / kSlotsPerKeyTile + kCombineCost) * 100 <= before * kWideGainPercent &&
-               slots * slot_bytes <= ARCKV_NOALLOC_MAX_WS_BYTES;
-      if (uneven) cap = lo;
-    }
   }
 
-  std::vector<Item> items, combines;
-  int64_t slot = 0;
-  for (const Tile& t : tiles) {
-    const int64_t nt = key_tiles(t);
-    const int64_t ns = uneven ? uneven_pieces(nt, cap) : (nt + cap - 1) / cap;
-    const int64_t group = static_cast<int64_t>(t.req) * num_kv_heads + t.kvh;
-    if (ns <= 1) {
-      items.push_back({{t.req, t.kvh, t.col_start, 0, t.kv_end, -1, 0, 0}, t.kv_end, group});
-      continue;
+  // ---- cutting the tiles, dealing the items to the XCDs, and the time a dealt plan takes -------
+  struct Cut {
+    std::vector<Item> items, combines;
+    int64_t slots = 0;
+    std::vector<std::vector<Item>> per_xcd;
+  };
+  auto cut_tiles = [&](int64_t F, bool uneven) {  // uneven: pieces of F key tiles and a remainder
+    Cut c;
+    for (const Tile& t : tiles) {
+      const int64_t nt = key_tiles(t);
+      const int64_t ns = uneven ? uneven_pieces(nt, F) : (nt + F - 1) / F;
+      const int64_t group = static_cast<int64_t>(t.req) * num_kv_heads + t.kvh;
+      if (ns <= 1) {
+        c.items.push_back({{t.req, t.kvh, t.col_start, 0, t.kv_end, -1, 0, 0}, t.kv_end, group});
+        continue;
+      }
+      for (int64_t s = 0; s < ns; ++s) {  // pieces of whole key tiles
+        const int64_t a_t = uneven ? s * F : s * nt / ns;
+        const int64_t b_t = uneven ? (s + 1 < ns ? (s + 1) * F : nt) : (s + 1) * nt / ns;
+        const int32_t a = static_cast<int32_t>(a_t * kKeyTile);
+        const int32_t b = static_cast<int32_t>(std::min<int64_t>(b_t * kKeyTile, t.kv_end));
+        c.items.push_back({{t.req, t.kvh, t.col_start, a, b, static_cast<int32_t>(c.slots + s), 0, 0}, b - a, group});
+      }
+      c.combines.push_back({{t.req, t.kvh, t.col_start, static_cast<int32_t>(c.slots), static_cast<int32_t>(ns), 0, 0, 0}, 0, group});
+      c.slots += ns;
     }
-    for (int64_t s = 0; s < ns; ++s) {  // pieces of whole key tiles
-      const int64_t a_t = uneven ? s * cap : s * nt / ns;
-      const int64_t b_t = uneven ? (s + 1 < ns ? (s + 1) * cap : nt) : (s + 1) * nt / ns;
-      const int32_t a = static_cast<int32_t>(a_t * kKeyTile);
-      const int32_t b = static_cast<int32_t>(std::min<int64_t>(b_t * kKeyTile, t.kv_end));
-      items.push_back({{t.req, t.kvh, t.col_start, a, b, static_cast<int32_t>(slot + s), 0, 0}, b - a, group});
-    }
-    combines.push_back({{t.req, t.kvh, t.col_start, static_cast<int32_t>(slot), static_cast<int32_t>(ns), 0, 0, 0}, 0, group});
-    slot += ns;
-  }
+    return c;
+  };
 
   // XCD-aware order: assign whole groups to XCDs (largest first, to the XCD that would finish
   // first: odd XCDs, measured about 5 % slower per key tile, count their work 2.5 % heavier and
   // even ones 2.5 % lighter), then emit position-major so work-group i runs on XCD i % 8; each
   // XCD's list is longest first.
-  const int64_t n_groups = static_cast<int64_t>(n_reqs) * num_kv_heads;  // group = req * hkv + kvh
-  std::vector<int64_t> cost_of(static_cast<size_t>(n_groups), 0);
-  std::vector<char> used(static_cast<size_t>(n_groups), 0);
-  for (const Item& it : items) {
-    cost_of[it.group] += it.cost;
-    used[it.group] = 1;
-  }
-  std::vector<std::pair<int64_t, int64_t>> groups;  // (group, cost)
-  for (int64_t g = 0; g < n_groups; ++g)
-    if (used[g]) groups.push_back({g, cost_of[g]});
-  std::sort(groups.begin(), groups.end(), [](const auto& a, const auto& b) {
-    return a.second != b.second ? a.second > b.second : a.first < b.first;
-  });
-  std::vector<int32_t> xcd_of(static_cast<size_t>(n_groups), 0);
-  int64_t load[kXcds] = {0};
-  auto finish = [&](int x, int64_t c) {   // relative finishing time with c more work
-    return (load[x] + c) * (x % 2 == 0 ? 1000 - kXcdSkewPermille : 1000 + kXcdSkewPermille);
-  };
-  for (const auto& g : groups) {
-    int best = 0;
-    for (int x = 1; x < kXcds; ++x) if (finish(x, g.second) < finish(best, g.second)) best = x;
-    xcd_of[g.first] = best;
-    load[best] += g.second;
-  }
-  std::vector<std::vector<Item>> per_xcd(kXcds);
-  if (groups.size() >= static_cast<size_t>(kXcds)) {
-    for (const Item& it : items) per_xcd[xcd_of[it.group]].push_back(it);
-  } else {  // fewer groups than XCDs: spread tiles over all XCDs instead
-    // An uneven cut pushes a tile's long pieces and its remainder one after the other; dealt in
-    // that order, tiles of one piece and a remainder would send every piece to an even XCD (1060
-    // tokens on 9918 cached, 32 / 4 heads: 34 pieces for 32 units, two rounds: 327 us, the equal
-    // cut 248).  Dealt longest first, every XCD gets its share of both: 190 us.
-    if (uneven)
-      std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
-    for (size_t i = 0; i < items.size(); ++i) per_xcd[i % kXcds].push_back(items[i]);
-  }
-  // Within an XCD: longest first (the tail of the launch is what load balance costs), but
-  // items whose key ranges are within ~10 % of each other count as equally long and are kept
-  // together by group, so that the work-groups running at the same time on the XCD are few
-  // groups' query tiles streaming the same keys and values, which the XCD's L2 serves once.
-  // The sort keys (length bucket, group rank, length) are computed once per item.
-  std::vector<int64_t> rank_of(static_cast<size_t>(n_groups), 0);
-  for (size_t g = 0; g < groups.size(); ++g) rank_of[groups[g].first] = static_cast<int64_t>(g);
-  auto bucket = [](int64_t cost) {  // log_{1.1} of the key-range length
-    return cost > 0 ? static_cast<int64_t>(std::log(static_cast<double>(cost)) / std::log(1.1)) : -1;
-  };
-  struct Key {
-    int64_t bucket, rank, cost;
-    int32_t idx;
-  };
-  std::vector<Key> keys;
-  std::vector<Item> sorted;
-  for (auto& v : per_xcd) {
-    keys.clear();
-    for (size_t i = 0; i < v.size(); ++i)
-      keys.push_back({bucket(v[i].cost), rank_of[v[i].group], v[i].cost, static_cast<int32_t>(i)});
-    std::stable_sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
-      if (a.bucket != b.bucket) return a.bucket > b.bucket;
-      return a.rank != b.rank ? a.rank < b.rank : a.cost > b.cost;
+  auto deal = [&](Cut& c, bool uneven) {
+    const int64_t n_groups = static_cast<int64_t>(n_reqs) * num_kv_heads;  // group = req * hkv + kvh
+    std::vector<int64_t> cost_of(static_cast<size_t>(n_groups), 0);
+    std::vector<char> used(static_cast<size_t>(n_groups), 0);
+    for (const Item& it : c.items) {
+      cost_of[it.group] += it.cost;
+      used[it.group] = 1;
+    }
+    std::vector<std::pair<int64_t, int64_t>> groups;  // (group, cost)
+    for (int64_t g = 0; g < n_groups; ++g)
+      if (used[g]) groups.push_back({g, cost_of[g]});
+    std::sort(groups.begin(), groups.end(), [](const auto& a, const auto& b) {
+      return a.second != b.second ? a.second > b.second : a.first < b.first;
     });
-    sorted.clear();
-    for (const Key& k : keys) sorted.push_back(v[k.idx]);
-    v.swap(sorted);
+    std::vector<int32_t> xcd_of(static_cast<size_t>(n_groups), 0);
+    int64_t load[kXcds] = {0};
+    auto finish = [&](int x, int64_t c) {   // relative finishing time with c more work
+      return (load[x] + c) * (x % 2 == 0 ? 1000 - kXcdSkewPermille : 1000 + kXcdSkewPermille);
+    };
+    for (const auto& g : groups) {
+      int best = 0;
+      for (int x = 1; x < kXcds; ++x) if (finish(x, g.second) < finish(best, g.second)) best = x;
+      xcd_of[g.first] = best;
+      load[best] += g.second;
+    }
+    c.per_xcd.assign(kXcds, {});
+    if (groups.size() >= static_cast<size_t>(kXcds)) {
+      for (const Item& it : c.items) c.per_xcd[xcd_of[it.group]].push_back(it);
+    } else {  // fewer groups than XCDs: spread tiles over all XCDs instead
+      // An uneven cut pushes a tile's long pieces and its remainder one after the other; dealt in
+      // that order, tiles of one piece and a remainder would send every piece to an even XCD (1060
+      // tokens on 9918 cached, 32 / 4 heads: 34 pieces for 32 units, two rounds: 327 us, the equal
+      // cut 248).  Dealt longest first, every XCD gets its share of both: 190 us.
+      if (uneven)
+        std::stable_sort(c.items.begin(), c.items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
+      for (size_t i = 0; i < c.items.size(); ++i) c.per_xcd[i % kXcds].push_back(c.items[i]);
+    }
+    // Within an XCD: longest first (the tail of the launch is what load balance costs), but
+    // items whose key ranges are within ~10 % of each other count as equally long and are kept
+    // together by group, so that the work-groups running at the same time on the XCD are few
+    // groups' query tiles streaming the same keys and values, which the XCD's L2 serves once.
+    // The sort keys (length bucket, group rank, length) are computed once per item.
+    std::vector<int64_t> rank_of(static_cast<size_t>(n_groups), 0);
+    for (size_t g = 0; g < groups.size(); ++g) rank_of[groups[g].first] = static_cast<int64_t>(g);
+    auto bucket = [](int64_t cost) {  // log_{1.1} of the key-range length
+      return cost > 0 ? static_cast<int64_t>(std::log(static_cast<double>(cost)) / std::log(1.1)) : -1;
+    };
+    struct Key {
+      int64_t bucket, rank, cost;
+      int32_t idx;
+    };
+    std::vector<Key> keys;
+    std::vector<Item> sorted;
+    for (auto& v : c.per_xcd) {
+      keys.clear();
+      for (size_t i = 0; i < v.size(); ++i)
+        keys.push_back({bucket(v[i].cost), rank_of[v[i].group], v[i].cost, static_cast<int32_t>(i)});
+      std::stable_sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
+        if (a.bucket != b.bucket) return a.bucket > b.bucket;
+        return a.rank != b.rank ? a.rank < b.rank : a.cost > b.cost;
+      });
+      sorted.clear();
+      for (const Key& k : keys) sorted.push_back(v[k.idx]);
+      v.swap(sorted);
+    }
+  };
+  // Time of a dealt plan in key tiles.  An XCD's work-groups go to its shader engines in turn, each
+  // to the unit of its engine that is free first (22 groups on 256 units: one engine got 6 pieces
+  // and 5 remainders for its 8 units, and the launch took 281 us where an even spread gives 200).
+  auto finish_time = [&](const Cut& c) -> int64_t {
+    const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
+    std::vector<int64_t> unit(static_cast<size_t>(target / (kXcds * engines)));
+    int64_t last = 0;
+    for (const auto& v : c.per_xcd)
+      for (int64_t e = 0; e < engines; ++e) {
+        std::fill(unit.begin(), unit.end(), 0);       // when each unit is free
+        for (size_t i = static_cast<size_t>(e); i < v.size(); i += static_cast<size_t>(engines)) {
+          int64_t& first = *std::min_element(unit.begin(), unit.end());
+          first += (v[i].cost + kKeyTile - 1) / kKeyTile + kWideItemCost;
+          last = std::max(last, first);
+        }
+      }
+    return last + (c.slots > 0 ? c.slots / kSlotsPerKeyTile + kCombineCost : 0);
+  };
+
+  Cut plan = cut_tiles(cap, false);
+  deal(plan, false);
+  if (base > 0 && base < target && target >= kXcds) {
+    // Equal pieces leave compute units idle where the tiles are more than half of them (192
+    // tiles on 256 units cannot be cut at all).  Instead, every tile can be cut into pieces of
+    // F key tiles, one per unit, and a remainder, several of which share a unit: the smallest F
+    // for which they fit (as many to a unit as the longest allows).  Whether that is worth it is
+    // decided on both plans as they are dealt.
+    const int64_t before = finish_time(plan);
+    // (every query tile comes once per KV head: the tiles' lengths are counted in such runs)
+    std::vector<int64_t> lengths;
+    for (size_t i = 0; i < tiles.size(); i += num_kv_heads) lengths.push_back(key_tiles(tiles[i]));
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    int64_t n_groups = 0;
+    for (int32_t r = 0; r < n_reqs; ++r) n_groups += cu_q[r + 1] > cu_q[r] ? num_kv_heads : 0;
+    // share of the items on one XCD (spread over all of them when the groups are fewer)
+    const int64_t on_one = n_groups >= kXcds ? up(n_groups, kXcds) : 1;
+    if (n_groups < kXcds) n_groups = kXcds;
+    const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
+    auto fits = [&](int64_t F) {
+      int64_t full = 0, rests = 0, longest = 0;
+      for (const int64_t nt : lengths) {
+        const int64_t k = uneven_pieces(nt, F), r = nt - (k - 1) * F;
+        full += (k - 1 + (r >= F)) * num_kv_heads;
+        rests += r < F ? num_kv_heads : 0;
+        longest = r < F ? std::max(longest, r) : longest;
+      }
+      const int64_t per_unit = (F + kWideItemCost) / (longest + kWideItemCost);  // >= 1
+      // counted for an engine of the XCD that gets most groups, if they are about equal
+      return up(up(full * on_one, n_groups), engines) + up(up(up(rests * on_one, n_groups), engines), per_unit) <=
+             target / (kXcds * engines);
+    };
+    int64_t lo = share, hi = (share + kWideItemCost + kCombineCost) * 100 <= before * kWideGainPercent ? cap : lo;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (fits(mid)) hi = mid; else lo = mid + 1;
+    }
+    const int64_t slot_bytes = kCols * (static_cast<int64_t>(head_dim) + 1) * 4;
+    int64_t slots = 0;
+    for (const int64_t nt : lengths) slots += uneven_pieces(nt, lo) > 1 ? uneven_pieces(nt, lo) * num_kv_heads : 0;
+    // (a piece of F key tiles alone takes this long: most cuts that gain nothing end here, undealt)
+    if (lo + kMinPiece <= arckv::kMaxItemKeys / kKeyTile && fits(lo) && slots * slot_bytes <= ARCKV_NOALLOC_MAX_WS_BYTES &&
+        (lo + kWideItemCost + slots / kSlotsPerKeyTile + kCombineCost) * 100 <= before * kWideGainPercent) {
+      Cut cut = cut_tiles(lo, true);
+      deal(cut, true);
+      if (finish_time(cut) * 100 <= before * kWideGainPercent) plan = std::move(cut);
+    }
   }
+
   size_t longest = 0;
-  for (auto& v : per_xcd) longest = std::max(longest, v.size());
+  for (auto& v : plan.per_xcd) longest = std::max(longest, v.size());
   std::vector<Item> ordered;
   ordered.reserve(longest * kXcds);
   for (size_t i = 0; i < longest; ++i)
     for (int x = 0; x < kXcds; ++x) {
-      if (i < per_xcd[x].size()) ordered.push_back(per_xcd[x][i]);
+      if (i < plan.per_xcd[x].size()) ordered.push_back(plan.per_xcd[x][i]);
       else ordered.push_back({{-1, 0, 0, 0, 0, -1, 0, 0}, 0, -1});  // idle slot keeps the XCD phase
     }
   // trailing idle slots carry no work; drop them
   while (!ordered.empty() && ordered.back().v[0] < 0) ordered.pop_back();
 
   *n_work = static_cast<int64_t>(ordered.size());
-  *n_combine = static_cast<int64_t>(combines.size());
-  *ws_bytes = slot * kCols * (static_cast<int64_t>(head_dim) + 1) * 4;
+  *n_combine = static_cast<int64_t>(plan.combines.size());
+  *ws_bytes = plan.slots * kCols * (static_cast<int64_t>(head_dim) + 1) * 4;
   if (work == nullptr) return ARCKV_OK;
   if (*n_work + *n_combine > work_cap)
     return arckv::fail(ARCKV_ENOSPC, "attention_plan: %lld items, capacity %lld",
                        (long long)(*n_work + *n_combine), (long long)work_cap);
   int32_t* w = work;
   for (const Item& it : ordered) { std::copy(it.v, it.v + ARCKV_WORK_INTS, w); w += ARCKV_WORK_INTS; }
-  for (const Item& it : combines) { std::copy(it.v, it.v + ARCKV_WORK_INTS, w); w += ARCKV_WORK_INTS; }
+  for (const Item& it : plan.combines) { std::copy(it.v, it.v + ARCKV_WORK_INTS, w); w += ARCKV_WORK_INTS; }
   return ARCKV_OK;
 }
