@@ -319,6 +319,8 @@ int32_t arckv_kv_scatter(void* k_pool, void* v_pool, const void* k_new, const vo
  * 256-column tiles: one work-group per item; long key ranges are split when the batch has too
  * few tiles to fill num_cus compute units (into one round of at most num_cus items, or of num_cus
  * units' worth of items where shorter ones share a unit).
+ * At head_dim 64 an odd *n_work (with an idle entry, request -1, where needed) lets two
+ * work-groups share a compute unit; the outputs are the same bits either way.
  * 128-column tiles: the items are grouped into lists of 8 entries (the list's items, then idle
  * entries with request -1), one list per work-group, balanced over at most num_cus lists;
  * key ranges are cut where a list's share ends.  Split tiles are merged by a log-sum-exp

@@ -62,6 +62,16 @@ constexpr int64_t kSlotsPerKeyTile = 18;
 constexpr int64_t kCombineCost = 2;
 constexpr int64_t kWideGainPercent = 90;
 
+// head_dim 64: an item beside another on its unit takes up to 1.7 times as long, and the pair less
+// than the two in turn.  That shortens a launch of several rounds and lengthens one that its longest
+// items fill: shared where the longest takes at most this much, in per cent, of the attention
+// kernel's estimated time.  Measured alone and shared, the longest item's part first: 12 prompts of
+// 1100 tokens, 16 / 16 heads, 34 %: 74 and 62 us; 17008 and 9344 cached, 527 and 753 new, 32 / 4,
+// 58 %: 261 and 229; 5 ragged turns, 64 / 8, 69 %: 234 and 225; one prompt of 1339 on 1248, 64 / 8,
+// 74 %: 60.7 and 60.8; 16 ragged turns, one on 60816, 40 / 8, 81 %: 632 and 681; 5 ragged turns, 16 / 8,
+// 256 items in 263 entries, 100 %: 237 and 294; an uneven cut, 600 on 30000, 64 / 8, 100 %: 337 and 397.
+constexpr int64_t kSharePercent = 70;
+
 // pieces of a tile of nt key tiles cut into pieces of F and a remainder; a remainder under
 // kMinPiece joins the piece before it
 int64_t uneven_pieces(int64_t nt, int64_t F) {
@@ -342,10 +352,11 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
       v.swap(sorted);
     }
   };
-  // Time of a dealt plan in key tiles.  An XCD's work-groups go to its shader engines in turn, each
+  // Time of a dealt plan in key tiles, with the partial results' way through memory and the combine
+  // or without.  An XCD's work-groups go to its shader engines in turn, each
   // to the unit of its engine that is free first (22 groups on 256 units: one engine got 6 pieces
   // and 5 remainders for its 8 units, and the launch took 281 us where an even spread gives 200).
-  auto finish_time = [&](const Cut& c) -> int64_t {
+  auto finish_time = [&](const Cut& c, bool with_combine) -> int64_t {
     const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
     std::vector<int64_t> unit(static_cast<size_t>(target / (kXcds * engines)));
     int64_t last = 0;
@@ -358,7 +369,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
           last = std::max(last, first);
         }
       }
-    return last + (c.slots > 0 ? c.slots / kSlotsPerKeyTile + kCombineCost : 0);
+    return last + (with_combine && c.slots > 0 ? c.slots / kSlotsPerKeyTile + kCombineCost : 0);
   };
 
   Cut plan = cut_tiles(cap, false);
@@ -369,7 +380,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
     // F key tiles, one per unit, and a remainder, several of which share a unit: the smallest F
     // for which they fit (as many to a unit as the longest allows).  Whether that is worth it is
     // decided on both plans as they are dealt.
-    const int64_t before = finish_time(plan);
+    const int64_t before = finish_time(plan, true);
     // (every query tile comes once per KV head: the tiles' lengths are counted in such runs)
     std::vector<int64_t> lengths;
     for (size_t i = 0; i < tiles.size(); i += num_kv_heads) lengths.push_back(key_tiles(tiles[i]));
@@ -406,7 +417,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
         (lo + kWideItemCost + slots / kSlotsPerKeyTile + kCombineCost) * 100 <= before * kWideGainPercent) {
       Cut cut = cut_tiles(lo, true);
       deal(cut, true);
-      if (finish_time(cut) * 100 <= before * kWideGainPercent) plan = std::move(cut);
+      if (finish_time(cut, true) * 100 <= before * kWideGainPercent) plan = std::move(cut);
     }
   }
 
@@ -421,6 +432,14 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
     }
   // trailing idle slots carry no work; drop them
   while (!ordered.empty() && ordered.back().v[0] < 0) ordered.pop_back();
+  // head_dim 64: whether two work-groups may share a compute unit, told to the launch by an odd
+  // number of entries (an idle one is added where the number is the other way).
+  if (head_dim == 64 && !ordered.empty()) {
+    int64_t longest_item = 0;
+    for (const Item& it : ordered) longest_item = std::max(longest_item, (it.cost + kKeyTile - 1) / kKeyTile);
+    const bool share_units = (longest_item + kWideItemCost) * 100 <= finish_time(plan, false) * kSharePercent;
+    if ((ordered.size() % 2 == 1) != share_units) ordered.push_back({{-1, 0, 0, 0, 0, -1, 0, 0}, 0, -1});
+  }
 
   *n_work = static_cast<int64_t>(ordered.size());
   *n_combine = static_cast<int64_t>(plan.combines.size());

@@ -640,8 +640,9 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // 16 conversation turns (1816 items of 31 steps) 432 -> 419 us.  At D = 64 (80 KiB of LDS, half
 // the MFMAs per exponential) two work-groups can share a compute unit, four waves per SIMD, so one
 // item's prologue runs beside the other's steps: 12 uncached prompts of 1100 tokens 78 -> 68 us.
-// PAIRED is that build (128 registers).  With no more items than units it would let the dispatcher
-// put two on one unit and leave another idle (3 turns on 2000 cached tokens: 57 us against 49).
+// PAIRED is that build (128 registers).  The plan asks for it with an odd number of entries, where
+// several rounds of items follow each other; elsewhere the dispatcher would put two items on one
+// unit and leave another idle (3 turns on 2000 cached tokens: 57 us against 49).
 // ANY takes queries and outputs that are not 16-byte aligned (a caller's view), through registers;
 // as a branch in the aligned build it cost the 16 conversation turns 3 %, all that the prologue gained.
 template <int D, int G, bool PAIRED, bool ANY>
@@ -1247,7 +1248,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   }
 }
 
-constexpr int64_t kUnits = 256;  // compute units of an MI355X
 constexpr int kWideNB = 1;  // 32-column MFMA blocks per wave on wide tiles
 constexpr int kWideWaves = arckv::kWideCols / (32 * kWideNB);
 static_assert(kWideWaves * 32 * kWideNB == arckv::kWideCols, "wide tile width");
@@ -1317,7 +1317,7 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
       hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false, true>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
-    else if (tile_cols == arckv::kWideCols && DD == 64 && n_work > kUnits)                     \
+    else if (tile_cols == arckv::kWideCols && DD == 64 && n_work % 2 == 1)                     \
       hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, DD == 64, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
