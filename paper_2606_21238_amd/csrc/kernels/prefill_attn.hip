@@ -87,6 +87,14 @@ template <int D>
 __device__ __forceinline__ int fk(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 __device__ __forceinline__ int sv(int d) { return (d >> 3) & 1; }
 
+// The lane's number, computed here and now: not a value that the compiler keeps in a register
+// from the start of the kernel on.
+__device__ __forceinline__ int lane_now() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // v_permlane32_swap(a, b) exchanges the upper half of a with the lower half of b.  With b = a,
@@ -640,7 +648,8 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // 16 conversation turns (1816 items of 31 steps) 432 -> 419 us.  At D = 64 (80 KiB of LDS, half
 // the MFMAs per exponential) two work-groups can share a compute unit, four waves per SIMD, so one
 // item's prologue runs beside the other's steps: 12 uncached prompts of 1100 tokens 78 -> 68 us.
-// PAIRED is that build (128 registers).  The plan asks for it with an odd number of entries, where
+// PAIRED is that build (128 registers; it spilled 9 to 11 before the epilogue took the lane's column
+// afresh).  The plan asks for it with an odd number of entries, where
 // several rounds of items follow each other; elsewhere the dispatcher would put two items on one
 // unit and leave another idle (3 turns on 2000 cached tokens: 57 us against 49).
 // ANY takes queries and outputs that are not 16-byte aligned (a caller's view), through registers;
@@ -833,7 +842,7 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
   // (group 0 only, 256 threads; published by the barrier that ends the half step)
   auto zero_v_tail = [&](int tile, int t0) {
     uint16_t* vb = reinterpret_cast<uint16_t*>(smem + (tile % kStages) * 2 * TILE + TILE);
-    for (int e = tid; e < kBK * D; e += kThreads / 2) {
+    for (int e = wave * 64 + lane_now(); e < kBK * D; e += kThreads / 2) {
       const int key = e & (kBK - 1), d = e / kBK;
       if (t0 + key >= L) {
         const int blk = key >> 4, kk = key & 15;
@@ -1052,11 +1061,15 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
   const float lse = lt > 0.f ? m_run + __log2f(lt) : -INFINITY;
 #pragma unroll
   for (int md = 0; md < DM; ++md) o[md] *= inv;
+  // the lane's column once more: PAIRED has no registers to hold it through the loops
+  const int le = lane_now(), r32 = le & 31, he = le >> 5;
+  const int ce = w.col_start + wave * 32 + r32;
+  const bool ve = ce < ncols && (q0 + ce / G) < n_q;
   if (w.slot < 0 && ncols - w.col_start <= kCols / 2) {
     // half of the tile or less (no second group): straight from registers, 34 prompts of 21 tokens
     // 15.2 us against 15.9 through LDS; on full tiles the same stores took 4 us per item
-    if (!cval) return;
-    uint16_t* dst = out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + col % G) * D;
+    if (!ve) return;
+    uint16_t* dst = out + (static_cast<int64_t>(q0 + ce / G) * hq + w.kvh * G + ce % G) * D;
 #pragma unroll
     for (int md = 0; md < DM; ++md)
 #pragma unroll
@@ -1064,7 +1077,7 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
         f32x4_t v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
-        *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * hg) = __builtin_convertvector(v, bf16x4_t);
+        *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * he) = __builtin_convertvector(v, bf16x4_t);
       }
     return;
   }
@@ -1082,11 +1095,11 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
         f32x4_t v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
-        *reinterpret_cast<bf16x4_t*>(ep + l32 * EP + (md * 32 + 8 * r4 + 4 * hg) * 2) = __builtin_convertvector(v, bf16x4_t);
+        *reinterpret_cast<bf16x4_t*>(ep + r32 * EP + (md * 32 + 8 * r4 + 4 * he) * 2) = __builtin_convertvector(v, bf16x4_t);
       }
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
-      const int r = i * QROWS + lane / (D / 8), ch = lane % (D / 8);
+      const int r = i * QROWS + le / (D / 8), ch = le % (D / 8);
       const int c = w.col_start + wave * 32 + r;
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(ep + r * EP + ch * 16);
       if (c < ncols && (q0 + c / G) < n_q)
@@ -1114,18 +1127,18 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
         f32x4_t v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = o[half * (DM / 2) + m][4 * r4 + jj];
-        *reinterpret_cast<f32x4_t*>(ep + l32 * EP + (m * 32 + 8 * r4 + 4 * hg) * 4) = v;
+        *reinterpret_cast<f32x4_t*>(ep + r32 * EP + (m * 32 + 8 * r4 + 4 * he) * 4) = v;
       }
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
-      const int r = i * QROWS + lane / (D / 8), ch = lane % (D / 8);
+      const int r = i * QROWS + le / (D / 8), ch = le % (D / 8);
       const int c = w.col_start + wave * 32 + r;
       const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ep + r * EP + ch * 16);
       if (c < ncols && (q0 + c / G) < n_q)
         *reinterpret_cast<f32x4_t*>(po + static_cast<int64_t>(r) * D + half * (D / 2) + ch * 4) = v;
     }
   }
-  if (cval && hg == 0) ws_lse[static_cast<int64_t>(w.slot) * kCols + wave * 32 + l32] = lse;
+  if (ve && he == 0) ws_lse[static_cast<int64_t>(w.slot) * kCols + wave * 32 + r32] = lse;
 }
 
 // Merges the key-range splits of one query tile: o = sum_s 2^(lse_s - M) O_s / sum_s 2^(lse_s - M)
