@@ -388,6 +388,8 @@ int32_t arckv_prepare_batch_hashed(arckv_cache* cache, const uint64_t* const* ha
  * device [n_reqs] (the same values given to arckv_attention_plan).  work: device copy of
  * the plan's items, tile_cols: the plan's tile width.  workspace: device, >= the planned
  * ws_bytes (may be NULL if 0).  Calls that overlap in time must not share a workspace.
+ * k_pool, v_pool and the workspace must be 16-byte aligned; q and out may start at
+ * any bf16 value (16-byte aligned ones are read and written faster).
  * A block-table entry outside [0, num_blocks) is never dereferenced: the kernel reads block 0
  * in its place, so the keys it covers get unspecified (finite or not) values; entries past a
  * request's last block (the -1 padding of a plan's rows) are not read at all.

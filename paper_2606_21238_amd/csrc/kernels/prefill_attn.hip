@@ -145,6 +145,20 @@ __device__ __forceinline__ void load_lds4(const void* g, lds_void* l) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(m) : "memory", "m0");
 }
 
+// Queries and outputs need not be 16-byte aligned (a caller's view): direct loads into LDS are only
+// given aligned addresses, and the kernels have a build (ANY) that takes the queries through
+// registers and stores without a claim on alignment.
+__device__ __forceinline__ void load_any16(const uint16_t* g, char* l) {
+  u32x4_t v;
+  __builtin_memcpy(&v, g, 16);
+  *reinterpret_cast<u32x4_t*>(l) = v;
+}
+template <bool ANY, class V>
+__device__ __forceinline__ void store_out(uint16_t* dst, const V& v) {
+  if constexpr (ANY) __builtin_memcpy(dst, &v, sizeof(V));
+  else *reinterpret_cast<V*>(dst) = v;
+}
+
 // Narrow tiles (128 query columns: short suffixes and decode-like batches) run as persistent
 // work-groups.  The host plan hands every work-group a list of up to kListItems items (its live
 // items first, then idle padding), balanced so that the lists of a launch carry about equal
@@ -157,7 +171,7 @@ __device__ __forceinline__ void load_lds4(const void* g, lds_void* l) {
 // [32 h, 32 h + 32) of every 64-key tile with its own online softmax, and at the end of an item
 // half 1 hands (m, l, O) to half 0 through the two ring stages that are free at that point.
 // Two waves share each SIMD, so one wave's exponentials overlap the other's MFMAs.
-template <int D, int G>
+template <int D, int G, bool ANY>
 __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
     const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
@@ -303,7 +317,9 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
       const int tok = gc / G, g = gc % G;
       const bool ok = gc < ld.ncols && (ld.q0 + tok) < n_q;
       const int64_t row = ok ? static_cast<int64_t>(ld.q0 + tok) * hq + ld.kvh * G + g : 0;
-      load_lds16(q + row * D + ((p ^ fk<D>(c)) * 8), (lds_void*)(st + j * LDB + wave * 1024));
+      const uint16_t* src = q + row * D + ((p ^ fk<D>(c)) * 8);
+      if constexpr (ANY) load_any16(src, st + b);     // waits for every older load; none is pending after it
+      else load_lds16(src, (lds_void*)(st + j * LDB + wave * 1024));
     }
   };
   auto prefetch_ph = [&]() {
@@ -605,7 +621,7 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
             f32x4_t v;
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] = o[md][4 * r4 + j] * inv;
-            *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * hg) = __builtin_convertvector(v, bf16x4_t);
+            store_out<ANY>(dst + md * 32 + 8 * r4 + 4 * hg, __builtin_convertvector(v, bf16x4_t));
           }
       } else if (it.slot < ws_slots) {
         const int local = cw * 32 + l32;
@@ -981,13 +997,8 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
       const bool ok = c < ncols && (q0 + c / G) < n_q;
       const int64_t row = ok ? static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G : 0;
       const uint16_t* src = q + row * D + (((lane % (D / 8)) ^ fk<D>(r)) * 8);
-      if constexpr (!ANY) {
-        load_lds16(src, (lds_void*)(qst + i * 1024));
-      } else {
-        u32x4_t v;
-        __builtin_memcpy(&v, src, 16);
-        *reinterpret_cast<u32x4_t*>(qst + i * 1024 + lane * 16) = v;
-      }
+      if constexpr (ANY) load_any16(src, qst + i * 1024 + lane * 16);
+      else load_lds16(src, (lds_void*)(qst + i * 1024));
     }
     issue_first(0);
     // With a second tile, tiles 1 and 2 always go out (2 past the key range: block 0 into a stage
@@ -1082,7 +1093,7 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
         f32x4_t v;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = o[md][4 * r4 + jj];
-        *reinterpret_cast<bf16x4_t*>(dst + md * 32 + 8 * r4 + 4 * he) = __builtin_convertvector(v, bf16x4_t);
+        store_out<ANY>(dst + md * 32 + 8 * r4 + 4 * he, __builtin_convertvector(v, bf16x4_t));
       }
     return;
   }
@@ -1108,11 +1119,7 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
       const int c = w.col_start + wave * 32 + r;
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(ep + r * EP + ch * 16);
       if (c < ncols && (q0 + c / G) < n_q)
-      {
-        uint16_t* dst = out + (static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G) * D + ch * 8;
-        if constexpr (ANY) __builtin_memcpy(dst, &v, 16);
-        else *reinterpret_cast<u32x4_t*>(dst) = v;
-      }
+        store_out<ANY>(out + (static_cast<int64_t>(q0 + c / G) * hq + w.kvh * G + c % G) * D + ch * 8, v);
     }
     return;
   }
@@ -1262,7 +1269,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     const int tok = col / G, g = col % G;
     if (q0 + tok >= n_q) continue;
     const bf16x4_t b = __builtin_convertvector(acc[k] * inv[e / D4], bf16x4_t);
-    *reinterpret_cast<bf16x4_t*>(out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + g) * D + 4 * d4) = b;
+    store_out<true>(out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + g) * D + 4 * d4, b);   // any alignment
   }
 }
 
@@ -1343,8 +1350,12 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
       hipLaunchKernelGGL((prefill_attn_pp_kernel<DD, GG, false, false>), grid, dim3(512), 0, st, kp, vp, qp, op, \
                          block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
+    else if (any_align)                                                                        \
+      hipLaunchKernelGGL((prefill_attn_list_kernel<DD, GG, true>), list_grid, dim3(512), 0, st, kp, vp, qp, \
+                         op, block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
+                         num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
     else                                                                                       \
-      hipLaunchKernelGGL((prefill_attn_list_kernel<DD, GG>), list_grid, dim3(512), 0, st, kp, vp, qp, \
+      hipLaunchKernelGGL((prefill_attn_list_kernel<DD, GG, false>), list_grid, dim3(512), 0, st, kp, vp, qp, \
                          op, block_tables, bt_stride, cu_q, seq_lens, n_reqs, wk, n_q, num_blocks, \
                          num_q_heads, num_kv_heads, scale_log2, ws_o, ws_lse, ws_slots);      \
   } while (0)

@@ -244,6 +244,39 @@ def test_wide_attention_of_views(d, hq, hkv, n):
     eng.release()
 
 
+VIEWS = [
+    ("decode lists", [(L, L - 1) for L in (1, 17, 300, 1300, 65, 2000)], 32, 8, 128, 256),
+    ("several items a list", [(L, L - 2) for L in (40, 129, 500, 33, 700, 90)], 16, 2, 64, 4),
+    ("short suffix lists, split", [(3000, 2984), (70, 54)], 40, 8, 128, 256),
+    ("wide, half a tile", [(200, 170)], 8, 1, 64, 256),
+    ("wide, whole tiles", [(700, 150), (130, 5)], 8, 2, 128, 256),
+    ("wide, split", [(2500, 2397)], 40, 8, 128, 40),
+    ("wide, split, d 64", [(1990, 1783)], 16, 8, 64, 24),
+]
+
+
+@pytest.mark.parametrize("offset", [1, 2, 4, 7])
+@pytest.mark.parametrize("what,reqs,hq,hkv,d,num_cus", VIEWS, ids=[v[0] for v in VIEWS])
+def test_attention_of_any_address(what, reqs, hq, hkv, d, num_cus, offset):
+    """Queries and outputs that start `offset` bf16 values into their storage: the bits of the
+    aligned call, and nothing written beside the output."""
+    print_case(f"{what}: hq={hq} hkv={hkv} d={d} num_cus={num_cus} offset={offset}")
+    b = build_batch(reqs, hq, hkv, d, seed=50 + d + offset)
+    want, ap = run_attention(b, hq, hkv, d, num_cus)
+    n = b["q"].numel()
+    qs = torch.empty(n + 8, dtype=b["q"].dtype, device=DEV)
+    os = torch.full((n + 16,), 7.0, dtype=b["q"].dtype, device=DEV)
+    q, out = qs[offset:offset + n].view(b["q"].shape), os[offset:offset + n].view(b["q"].shape)
+    q.copy_(b["q"])
+    ws = torch.zeros(max(ap.ws_bytes, 1), dtype=torch.uint8, device=DEV)
+    dev = [torch.from_numpy(x).to(DEV) for x in (b["bt"], b["cu"], b["seq"], ap.work)]
+    ak.prefill_attention(b["kp"], b["vp"], q, out, *dev, ap.n_work, ap.n_combine, ap.tile_cols, d ** -0.5, ws,
+                         ap.ws_bytes)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(out), want)
+    assert bool((os[:offset] == 7).all()) and bool((os[offset + n:] == 7).all())
+
+
 # Scores that grow, jump or spike along the keys, so that the running maximum moves after the
 # first key tile of an item (the online softmax's rescale), and scores that fall (it never
 # does).  With N(0, 1) inputs a 128-dim score has a standard deviation of about 1.4 in log2
