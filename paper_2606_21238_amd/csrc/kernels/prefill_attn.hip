@@ -1332,7 +1332,8 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
     return ev == nullptr || hipEventRecord(ev, st) == hipSuccess;
   };
   if (!record(ev_begin)) return arckv::fail(ARCKV_EDEVICE, "prefill_attention: event record failed");
-  if (n_work > 0) {
+  const bool any_rows = n_q > 0;   // without one nothing is computed, whatever the work items name: q holds no row to read
+  if (n_work > 0 && any_rows) {
     const dim3 grid(static_cast<unsigned>(n_work));
     const bool any_align = (reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(out)) % 16 != 0;
     const dim3 list_grid(static_cast<unsigned>(n_work / arckv::kListItems));
@@ -1382,7 +1383,7 @@ int32_t prefill_attention(const void* k_pool, const void* v_pool, const void* q,
       return arckv::fail(ARCKV_EDEVICE, "prefill_attention: %s", hipGetErrorString(e));
   }
   if (!record(ev_mid)) return arckv::fail(ARCKV_EDEVICE, "prefill_attention: event record failed");
-  if (n_combine > 0) {
+  if (n_combine > 0 && any_rows) {
     const dim3 grid(static_cast<unsigned>(n_combine), static_cast<unsigned>(tile_cols / kCombineCols));
     const Work* items = wk + n_work;
     if (head_dim == 64)

@@ -277,6 +277,24 @@ def test_attention_of_any_address(what, reqs, hq, hkv, d, num_cus, offset):
     assert bool((os[:offset] == 7).all()) and bool((os[offset + n:] == 7).all())
 
 
+@pytest.mark.parametrize("S", [300, 16])     # wide tiles, narrow lists
+def test_attention_without_query_rows(S):
+    """n_q = 0 with work items that name a request's tokens: accepted, and nothing is run."""
+    print_case(f"no query rows, S={S}")
+    b = build_batch([(1000, 1000 - S)], 8, 2, 128, seed=3)
+    ap = ak.attention_plan(b["cu"], b["seq"], 8, 2, 128, 256)
+    assert ap.tile_cols == (256 if S == 300 else 128) and ap.n_combine > 0
+    out = torch.full_like(b["q"], 7.0)
+    ws = torch.zeros(ap.ws_bytes, dtype=torch.uint8, device=DEV)
+    bt, cu, sl, wk = (torch.from_numpy(x).to(DEV) for x in (b["bt"], b["cu"], b["seq"], ap.work))
+    st = ak.lib().arckv_prefill_attention(
+        b["kp"].data_ptr(), b["vp"].data_ptr(), b["q"].data_ptr(), out.data_ptr(), bt.data_ptr(), bt.shape[1],
+        cu.data_ptr(), sl.data_ptr(), 1, 0, b["kp"].shape[0], wk.data_ptr(), ap.n_work, ap.n_combine, ap.tile_cols,
+        8, 2, 128, 128 ** -0.5, ws.data_ptr(), ap.ws_bytes, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert st == 0 and bool((out == 7).all()) and not bool(ws.any())
+
+
 # Scores that grow, jump or spike along the keys, so that the running maximum moves after the
 # first key tile of an item (the online softmax's rescale), and scores that fall (it never
 # does).  With N(0, 1) inputs a 128-dim score has a standard deviation of about 1.4 in log2
