@@ -6,8 +6,8 @@
 //   q, k = rotary(y_q, y_k) at each token's absolute position; v = y_v
 //
 // One kernel does the projection and the rotation, so y never goes to memory:
-//  * qkv_gemm_rope_kernel (prefill batches): 256- or 128-token x 256-output tiles, 4 waves, one
-//    per SIMD, rotation in registers;
+//  * qkv_gemm_rope_kernel (prefill batches): 256-, 192- or 128-token x 256-output tiles, 4 waves,
+//    one per SIMD, rotation in registers;
 //  * qkv_ksplit_kernel (decode steps, short questions): 32- or 64-token x 32- or 64-output tiles
 //    whose waves split H.
 // Both use v_mfma_f32_32x32x16_bf16 and stream x and W global -> LDS with 16-byte direct loads
@@ -202,10 +202,10 @@ __device__ __forceinline__ void store_tile(const char* ep, int pitch, int t0, in
 // tile writes took every LDS cycle the MFMAs left); with one wave per SIMD the accumulators
 // (256 registers) and two sets of operands fit, so a step's MFMAs run with the next step's
 // operand reads and the loads between them, one barrier per 64 columns.  x tiles have a ring
-// of three stages; W tiles of WS = 2 at TM = 256 (160 KiB in all), where a stage takes as long as
-// a load, and of 3 at TM = 128 (144 KiB): its stages are half as long, and W requested 3/4 of a
-// stage ahead bound them (907 tokens x 5120 x 7168: 91.7 us with 2, 80.7 with 3; 512 x 8192 x
-// 10240: 129 and 112).
+// of three stages; W tiles of WS = 2 at TM = 256 (160 KiB in all) and 192 (136 KiB), where a stage
+// takes as long as a load, and of 3 at TM = 128 (144 KiB): its stages are half as long, and W
+// requested 3/4 of a stage ahead bound them (907 tokens x 5120 x 7168: 91.7 us with 2, 80.7 with 3;
+// 512 x 8192 x 10240: 129 and 112).
 //
 // Stage s, four steps of 16 columns (the operands of a step are read during the step before):
 //   step 0       requests x(s + 2), into the buffer of x(s - 1)
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
     step(1, [&](int i) __attribute__((always_inline)) { return rd(xn * XB, wn, 0, i); },
          [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-           for (int k = 0; k < WL / (2 * MB); ++k) issue_w(s + WS, wb, i * (WL / (2 * MB)) + k);
+           for (int k = i * WL / (2 * MB); k < (i + 1) * WL / (2 * MB); ++k) issue_w(s + WS, wb, k);
          });
     __builtin_amdgcn_sched_barrier(0);
     x3 = xn;
@@ -612,10 +612,14 @@ namespace {
 //             46.9 with 64 x 32; before 97 and 137), else 64 x 32 (hidden 1024, 3072 outputs,
 //             T = 256: 10.2 against 13.5).  Past that the prefill kernel's reuse wins: hidden 8192,
 //             T = 512 (5 tiles per unit): 112 against 149; hidden 5120, T = 450 (3.5): 78 against 76
-//   prefill   128-token tiles when they need fewer rounds of the chip for their 0.6 to 0.7 of a
-//             256-token tile's time: hidden 5120, T = 907: 81 against 119 (one round each); T = 3000
-//             (3 and 2 rounds): 222 against 233; T = 2000 (2 and 1): 158 against 132
-enum class QkvRoute { kK32x32Wide, kK32x32, kK64x32, kK64x64, kG128, kG256 };
+//   prefill   the tile height whose rounds of the chip take least, a round of 128-, 192- and
+//             256-token tiles counted as 3, 4 and 5 (T = 907: 58, 70 and 84 us, one round each).
+//             T = 1500: 112 us with 128 (2 rounds), 80 with 192 (1), 86 with 256 (1; the tiles before
+//             84); T = 2000 (2, 2, 1): 117, 153 and 98; T = 2600 (2, 2, 2): 132, 157, 191; T = 3300 (3, 2,
+//             2): 181, 164, 194; hidden 1024, 3072 outputs, T = 3300 (2, 1, 1): 43, 34 and 38 (before: 36).
+//             Not 192 where its last tiles pad the tokens by over 10 % more than 256 does: hidden
+//             8192, T = 1004 (1152 and 1024 tokens, one round each): 157 and 154
+enum class QkvRoute { kK32x32Wide, kK32x32, kK64x32, kK64x64, kG128, kG192, kG256 };
 constexpr int64_t kUnits = 256;   // compute units of an MI355X
 QkvRoute qkv_route(int64_t n_tokens, int64_t hidden, int64_t n_out) {
   auto tiles = [&](int64_t m, int64_t n) { return ((n_tokens + m - 1) / m) * ((n_out + n - 1) / n); };
@@ -623,8 +627,11 @@ QkvRoute qkv_route(int64_t n_tokens, int64_t hidden, int64_t n_out) {
   if (n_tokens <= 64) return QkvRoute::kK32x32;
   if (2 * tiles(64, 64) <= 7 * kUnits)
     return hidden > 2048 && 4 * tiles(64, 64) >= 3 * kUnits ? QkvRoute::kK64x64 : QkvRoute::kK64x32;
-  auto rounds = [&](int64_t m) { return (tiles(m, kTN) + kUnits - 1) / kUnits; };
-  return 3 * rounds(128) < 5 * rounds(256) ? QkvRoute::kG128 : QkvRoute::kG256;
+  auto time = [&](int64_t m, int64_t each) { return each * ((tiles(m, kTN) + kUnits - 1) / kUnits); };
+  const int64_t t128 = time(128, 3), t192 = time(192, 4), t256 = time(256, 5);
+  const bool pads = 192 * tiles(192, kTN) * 10 > 256 * tiles(256, kTN) * 11;
+  if (t256 <= t128 && (t256 <= t192 || pads)) return QkvRoute::kG256;
+  return t192 <= t128 && !pads ? QkvRoute::kG192 : QkvRoute::kG128;
 }
 
 // Shared by arckv_qkv_rope and arckv_qkv_rope_to_pool: pool == true writes K and V into the
@@ -692,6 +699,7 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
     };
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
     using I4 = std::integral_constant<int, 4>;
     using I8 = std::integral_constant<int, 8>;
     switch (qkv_route(n_tokens, hidden, n_out)) {
@@ -700,6 +708,7 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
       case QkvRoute::kK64x32: ksplit(I2{}, I1{}, I4{}, I1{}); break;
       case QkvRoute::kK64x64: ksplit(I2{}, I2{}, I4{}, I1{}); break;
       case QkvRoute::kG128: gemm(I2{}); break;
+      case QkvRoute::kG192: gemm(I3{}); break;
       case QkvRoute::kG256: gemm(I4{}); break;
     }
   };

@@ -216,8 +216,12 @@ ROUTES = [
     ("128-token tiles, ragged", [(2390, 0)], 96, 8, 2, 128),
     ("128-token tiles, the rings go round", [(2390, 7)], 416, 8, 2, 128),
     ("128-token tiles, d 64, half an output tile", [(2301, 1), (257, 100)], 64, 22, 2, 64),
-    ("256-token tiles, ragged", [(6001, 0), (500, 170)], 160, 8, 2, 128),
-    ("256-token tiles, d 64, one stage", [(6000, 0), (331, 1)], 32, 20, 2, 64),
+    ("192-token tiles, ragged", [(6001, 0), (500, 170)], 160, 8, 2, 128),
+    ("192-token tiles, d 64, one stage", [(6000, 0), (331, 1)], 32, 20, 2, 64),
+    ("192-token tiles, the rings go round", [(5475, 3), (100, 90)], 480, 8, 2, 128),
+    ("192-token tiles, d 64, half an output tile", [(4500, 0), (705, 1)], 96, 22, 2, 64),
+    ("256-token tiles, ragged, half a stage at the end", [(8100, 0), (500, 170)], 160, 8, 2, 128),
+    ("256-token tiles, d 64, one stage", [(8065, 0), (33, 1)], 32, 20, 2, 64),
 ]
 
 
