@@ -17,14 +17,21 @@
 // consecutive tokens of one dimension per store instruction.  Bytes are copied, never converted:
 // the result is bit-exact.  Slots outside the pool are skipped.
 //
-// What bounds it is memory, and the chain slots -> barrier -> load -> store before it was cut: the
-// rows do not depend on the slots, so a thread asks for all of its chunks first.  The rows are
-// read once and non-temporally, which leaves the caches to the pools that attention reads next.
-// 24898 tokens of 8 heads of 128 (204 MB): 47.0 us, 42.4 with the early loads and the paired runs,
-// 40.3 with non-temporal loads too (5.1 TB/s, a large copy reaches 5.0), and a pass over the pool
-// right after it 34.9, 36.6 and 30.8 us.  13390 tokens of 16 heads of 64: 26.2, 24.4, 20.6.
+// What bounds it is memory, and the chain slots -> barrier -> load -> store: the rows do not depend
+// on the slots, so a thread asks for all of its chunks first.  Whole rows are read once and
+// non-temporally, which leaves the caches to the pools that attention reads next.
+// 24898 tokens of 8 heads of 128 (204 MB), rows and pool out of the caches: 51 us before, 42.4 with
+// the early loads and the paired runs, 40.3 with non-temporal loads too (5.1 TB/s, a large copy
+// reaches 5.0), and a pass over the pool right after it 34.9, 36.6 and 30.8 us.  13390 tokens of 16
+// heads of 64: 26.2, 24.4, 20.6.  Rows that the caches still hold cost more that way: 9000 tokens of
+// 8 heads of 128 just written by another kernel, 16.5 us before, 16.2 with plain loads, 17.6; at 24000
+// tokens of 16 heads they do not fit any more: 89, 87 and 80.
 // (Non-temporal stores as well: 38.2 us, but slots that straddle the work-groups' 64 tokens 46.7
 // against 45.4 and head_dim 64 21.3 with a slower pass after it.)
+// Sliced rows are read with plain loads (four work-groups share a line), their runs are not paired
+// (1000 unrelated slots, 16 heads of 128: 47.5 us paired, 42.8), and the rows come first only where
+// the launch has few work-groups, at most four per compute unit of 256 (64 decode slots of 16 heads of
+// 128: 8.4 -> 8.0 us; 1000 tokens in runs: 8.6 with the rows first, 8.2 with the slots first, 8.0 before).
 #include <hip/hip_runtime.h>
 
 #include "../host/internal.hpp"
@@ -38,17 +45,22 @@ constexpr int kMaxRuns = kTok / 8;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ u32x4_t load_once(const uint16_t* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+// 16 bytes of a row: whole rows are read once and non-temporally; of a sliced row the other
+// work-groups read the rest of the line
+template <bool WHOLE>
+__device__ __forceinline__ u32x4_t load_row(const uint16_t* p) {
+  if constexpr (WHOLE) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+  else return *reinterpret_cast<const u32x4_t*>(p);
 }
 
-template <int D, int DPW>
+template <int D, int DPW, bool EARLY>
 __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
     uint16_t* __restrict__ k_pool, uint16_t* __restrict__ v_pool,
     const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
     const int32_t* __restrict__ slots, int64_t n_tokens, int64_t n_slots, int hkv) {
   constexpr int CH = DPW / 8;          // 16-byte chunks of a row slice
   constexpr int VROW = DPW + 2;        // padded LDS row (u16): column reads spread over banks
+  constexpr bool kWhole = DPW == D;
   __shared__ uint32_t sv32[kTok * VROW / 2];
   __shared__ int32_t sslot[kTok];
   __shared__ int32_t run_tok[kMaxRuns], run_slot[kMaxRuns];
@@ -66,11 +78,11 @@ __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int c = tid + i * kThreads;
-    if (c < kChunks) {
+    if (c < kChunks && EARLY) {
       const int64_t t = min(t0 + c / CH, n_tokens - 1);
       const int64_t src = (t * hkv + h) * D + d0 + (c % CH) * 8;
-      kv[i] = load_once(k_new + src);
-      vv[i] = load_once(v_new + src);
+      kv[i] = load_row<kWhole>(k_new + src);
+      vv[i] = load_row<kWhole>(v_new + src);
     }
   }
   if (tid < kTok) {
@@ -97,6 +109,16 @@ __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
       n_runs = __builtin_popcountll(m);
     }
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int c = tid + i * kThreads;
+    if (c < kChunks && !EARLY) {
+      const int64_t t = min(t0 + c / CH, n_tokens - 1);
+      const int64_t src = (t * hkv + h) * D + d0 + (c % CH) * 8;
+      kv[i] = load_row<kWhole>(k_new + src);
+      vv[i] = load_row<kWhole>(v_new + src);
+    }
+  }
   // V into LDS (row = token, padded), K straight to its slots
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -117,12 +139,13 @@ __global__ __launch_bounds__(kThreads) void kv_scatter_kernel(
     }
   }
   __syncthreads();
-  // V of the runs: (pair of runs, dimension, run of the pair) per thread; where the first run is
-  // the upper half of a block, the pairs start one run earlier
+  // V of the runs.  Whole rows: (pair of runs, dimension, run of the pair) per thread; where the
+  // first run is the upper half of a block, the pairs start one run earlier.  Sliced: (run, dimension).
   const int nr = n_runs;
-  const int odd = nr > 0 ? (run_slot[0] >> 3) & 1 : 0;
-  for (int e = tid; e < (nr + odd + 1) / 2 * (2 * DPW); e += kThreads) {
-    const int r = e / (2 * DPW) * 2 + (e & 1) - odd, dl = (e >> 1) % DPW, d = d0 + dl;
+  const int odd = kWhole && nr > 0 ? (run_slot[0] >> 3) & 1 : 0;
+  for (int e = tid; e < (kWhole ? (nr + odd + 1) / 2 * (2 * DPW) : nr * DPW); e += kThreads) {
+    const int r = kWhole ? e / (2 * DPW) * 2 + (e & 1) - odd : e / DPW;
+    const int dl = (kWhole ? e >> 1 : e) % DPW, d = d0 + dl;
     if (r < 0 || r >= nr) continue;
     const int tl = run_tok[r];
     const int32_t sb = run_slot[r];
@@ -164,7 +187,8 @@ extern "C" int32_t arckv_kv_scatter(void* k_pool, void* v_pool, const void* k_ne
   for (const void* p : {static_cast<const void*>(k_pool), static_cast<const void*>(v_pool), k_new, v_new})
     if (reinterpret_cast<uintptr_t>(p) % 16 != 0)
       return arckv::fail(ARCKV_EINVAL, "kv_scatter: pools and new rows must be 16-byte aligned");
-  // small batches (decode) split the head dimension finely to spread over more work-groups
+  // small batches (decode) split the head dimension finely to spread over more work-groups; the
+  // rows are asked for before the slots where these are few
   const bool small = n_tokens <= 1024;
   const int dpw = small ? 16 : head_dim;
   const dim3 grid(static_cast<unsigned>((n_tokens + kTok - 1) / kTok), num_kv_heads,
@@ -175,13 +199,14 @@ extern "C" int32_t arckv_kv_scatter(void* k_pool, void* v_pool, const void* k_ne
   auto* kn = static_cast<const uint16_t*>(k_new);
   auto* vn = static_cast<const uint16_t*>(v_new);
   const int64_t n_slots = num_blocks * 16;
-#define ARCKV_SCATTER(DD, PW)                                                               \
-  hipLaunchKernelGGL((kv_scatter_kernel<DD, PW>), grid, dim3(kThreads), 0, st, kp, vp, kn, vn, \
+  const bool few = static_cast<int64_t>(grid.x) * grid.y * grid.z <= 1024;
+#define ARCKV_SCATTER(DD, PW, EE)                                                           \
+  hipLaunchKernelGGL((kv_scatter_kernel<DD, PW, EE>), grid, dim3(kThreads), 0, st, kp, vp, kn, vn, \
                      slot_mapping, n_tokens, n_slots, num_kv_heads)
   if (head_dim == 64) {
-    if (small) ARCKV_SCATTER(64, 16); else ARCKV_SCATTER(64, 64);
+    if (!small) ARCKV_SCATTER(64, 64, true); else if (few) ARCKV_SCATTER(64, 16, true); else ARCKV_SCATTER(64, 16, false);
   } else {
-    if (small) ARCKV_SCATTER(128, 16); else ARCKV_SCATTER(128, 128);
+    if (!small) ARCKV_SCATTER(128, 128, true); else if (few) ARCKV_SCATTER(128, 16, true); else ARCKV_SCATTER(128, 16, false);
   }
 #undef ARCKV_SCATTER
   const hipError_t e = hipGetLastError();

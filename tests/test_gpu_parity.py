@@ -92,6 +92,30 @@ def test_scatter_block_runs_bit_exact(d, hkv, n, start):
     assert np.array_equal(bits(eng_v), vp)
 
 
+@pytest.mark.parametrize("d,hkv,n", [(128, 16, 512), (128, 16, 513), (64, 32, 512), (64, 32, 1024), (128, 11, 1000)])
+def test_scatter_of_sliced_rows_bit_exact(d, hkv, n):
+    """Up to 1024 tokens a work-group takes 16 dimensions, its rows before the slots with at most
+    1024 work-groups and after them with more: runs, broken runs and single slots on both sides."""
+    print_case(f"scatter sliced d={d} hkv={hkv} n={n}")
+    rng = np.random.default_rng(n + d)
+    nblk = n // 16 + 80
+    perm = rng.permutation(nblk * 2)[:nblk].astype(np.int64)
+    j = np.arange(n) + 3
+    slots = (perm[j // 16] * 16 + j % 16).astype(np.int32)
+    slots[::37] = -1
+    slots[5::41] = (nblk * 2 + np.arange(len(slots[5::41]))) * 16 + 9      # blocks of their own
+    nphys = nblk * 2 + len(slots[5::41])
+    k_new, v_new = randn_bf16((n, hkv, d), n), randn_bf16((n, hkv, d), n + 1)
+    kp = torch.full((nphys, hkv, 16, d), -1, dtype=torch.int16, device=DEV)
+    vp = torch.full((nphys, hkv, d, 16), -1, dtype=torch.int16, device=DEV)
+    ak.kv_scatter(kp, vp, k_new, v_new, torch.from_numpy(slots).to(DEV))
+    torch.cuda.synchronize()
+    okp, ovp = okv.new_pool(nphys, hkv, d)
+    keep = slots >= 0
+    okv.scatter(okp, ovp, bits(k_new)[keep], bits(v_new)[keep], slots[keep])
+    assert np.array_equal(bits(kp), okp) and np.array_equal(bits(vp), ovp)
+
+
 # ------------------------------------------------------------------------------------------
 # attention on directly built batches (random placement, edge lengths)
 # ------------------------------------------------------------------------------------------
