@@ -461,6 +461,12 @@ int32_t arckv_qkv_rope(const void* x, const void* w_qkv, int64_t n_tokens, int32
                        double rope_theta, void* workspace, int64_t ws_bytes, void* q_out,
                        void* k_out, void* v_out, void* stream);
 
+/* TEST ONLY.  The tile (tokens x outputs) that a producer call of these sizes takes, and the waves
+ * among which its work-groups split hidden (0: none), so that a test can tell which kernel it
+ * runs.  Host only. */
+int32_t arckv_test_qkv_tiles(int64_t n_tokens, int32_t hidden, int64_t n_out, int32_t* tile_tokens,
+                             int32_t* tile_outputs, int32_t* split_waves);
+
 /* The same producer with the KV scatter fused into it: Q as arckv_qkv_rope writes it, and K
  * and V of token t written straight into the paged pools at slot_mapping[t] (layout V1, as
  * arckv_kv_scatter writes them: pool[slot] <- the token's rotated K row and its V row), so

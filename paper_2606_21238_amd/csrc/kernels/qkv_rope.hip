@@ -726,6 +726,24 @@ int32_t qkv_rope_launch(const char* fn, const void* x, const void* w_qkv, int64_
 
 }  // namespace
 
+extern "C" int32_t arckv_test_qkv_tiles(int64_t n_tokens, int32_t hidden, int64_t n_out, int32_t* tile_tokens,
+                                        int32_t* tile_outputs, int32_t* split_waves) {
+  if (n_tokens < 1 || n_tokens > INT32_MAX || hidden < 1 || n_out < 1 || n_out > INT32_MAX ||
+      tile_tokens == nullptr || tile_outputs == nullptr || split_waves == nullptr)
+    return arckv::fail(ARCKV_EINVAL, "test_qkv_tiles: bad arguments");
+  auto set = [&](int32_t m, int32_t n, int32_t w) { *tile_tokens = m; *tile_outputs = n; *split_waves = w; };
+  switch (qkv_route(n_tokens, hidden, n_out)) {
+    case QkvRoute::kK32x32Wide: set(32, 32, 8); break;
+    case QkvRoute::kK32x32: set(32, 32, 4); break;
+    case QkvRoute::kK64x32: set(64, 32, 4); break;
+    case QkvRoute::kK64x64: set(64, 64, 4); break;
+    case QkvRoute::kG128: set(128, kTN, 0); break;
+    case QkvRoute::kG192: set(192, kTN, 0); break;
+    case QkvRoute::kG256: set(256, kTN, 0); break;
+  }
+  return ARCKV_OK;
+}
+
 extern "C" int32_t arckv_qkv_rope(const void* x, const void* w_qkv, int64_t n_tokens, int32_t hidden,
                                   int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                                   const int32_t* cu_q, const int32_t* seq_lens, int32_t n_reqs,

@@ -10,6 +10,8 @@ reduced in fp64 add ~1e-6 of the pair's norm.  Values are not rotated.
 
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -225,10 +227,20 @@ ROUTES = [
 ]
 
 
+def qkv_tiles(n_tokens, hidden, n_out):
+    """(tokens, outputs, waves that split hidden) of the tile that a call of these sizes takes."""
+    v = [ctypes.c_int32() for _ in range(3)]
+    assert ak.lib().arckv_test_qkv_tiles(n_tokens, hidden, n_out, *map(ctypes.byref, v)) == 0
+    return tuple(x.value for x in v)
+
+
 @pytest.mark.parametrize("what,reqs,hidden,hq,hkv,d", ROUTES, ids=[r[0] for r in ROUTES])
 def test_qkv_rope_every_kernel(what, reqs, hidden, hq, hkv, d):
     """Rows against the oracle, and the pool variant bit for bit against those rows."""
     print_case(f"{what}: hidden={hidden} hq={hq} hkv={hkv} d={d}")
+    tile, outputs, waves = qkv_tiles(sum(L - P for L, P in reqs), hidden, (hq + 2 * hkv) * d)
+    assert what.startswith(f"{tile}x{outputs} tiles" if waves else f"{tile}-token tiles")
+    assert "waves" not in what or f"{waves} waves" in what
     r = run(reqs, hidden, hq, hkv, d, seed=31 + hidden)
     check(r, hq, hkv, d)
     T = r["q"].shape[0]
