@@ -23,6 +23,7 @@ from tests.test_gpu_parity import DEV, build_batch, oracle_out, run_attention  #
 @pytest.mark.parametrize("reqs,hq,hkv,d", [
     ([(L, L - 1) for L in (300, 4097, 2000, 65, 1500, 777, 9000, 33)], 32, 8, 128),  # lists
     ([(1040, 1024), (600, 500), (3000, 2900)], 32, 8, 128),                           # wide tiles
+    ([(2500, 2000)] * 5, 4, 2, 64),                  # wide tiles, two work-groups per unit
 ])
 def test_captured_attention_replays_equal_the_eager_call(reqs, hq, hkv, d):
     if not torch.cuda.is_available():
@@ -31,6 +32,7 @@ def test_captured_attention_replays_equal_the_eager_call(reqs, hq, hkv, d):
     b = build_batch(reqs, hq, hkv, d, seed=810 + len(reqs))
     want, ap = run_attention(b, hq, hkv, d, 256)
     assert ap.n_combine > 0 and ap.ws_bytes <= ak.NOALLOC_MAX_WS_BYTES
+    assert d == 128 or ap.n_work % 2 == 1
     bt = torch.from_numpy(b["bt"]).to(DEV)
     cu = torch.from_numpy(b["cu"]).to(DEV)
     seq = torch.from_numpy(b["seq"]).to(DEV)

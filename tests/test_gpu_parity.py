@@ -346,6 +346,46 @@ def test_attention_moving_maxima(case, num_cus):
         compare(got, oracle_out(b, hq, hkv, d), f"{name}, {reqs}")
 
 
+# head_dim 64 plans whose work-groups share compute units (an odd number of entries): every group
+# size, whole tiles and cut ones, with scores of every kind in RESCALE and plain ones.
+SHARED = [
+    ([(700, 0), (333, 20)], 8, 8, 32, True),
+    ([(1500, 1000), (700, 100)], 8, 4, 16, False),
+    ([(4000, 3800), (700, 0), (300, 0), (400, 0)], 8, 2, 16, True),
+    ([(500, 0)] * 3 + [(2200, 2000)], 5, 1, 8, False),
+    ([(2500, 2300)] + [(500, 0)] * 4, 16, 2, 32, True),
+]
+
+
+@pytest.mark.parametrize("gain", [None] + list(range(len(RESCALE))))
+@pytest.mark.parametrize("reqs,hq,hkv,num_cus,split", SHARED)
+def test_attention_of_paired_work_groups(reqs, hq, hkv, num_cus, split, gain):
+    print_case(f"paired {reqs} hq={hq} hkv={hkv} num_cus={num_cus} gain={gain}")
+    name, k_gain = RESCALE[gain] if gain is not None else ("plain", None)
+    b = build_batch(reqs, hq, hkv, 64, seed=2100 + hq, k_gain=k_gain, v_gain=1.0 if gain is None else 0.25)
+    got, ap = run_attention(b, hq, hkv, 64, num_cus)
+    assert ap.tile_cols == 256 and ap.n_work % 2 == 1 and (ap.n_combine > 0) == split
+    compare(got, oracle_out(b, hq, hkv, 64), f"paired work-groups, {name}")
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (32, 8, 128), (8, 1, 128), (4, 2, 64), (40, 8, 64)])
+def test_attention_items_of_two_key_tiles(hq, hkv, d):
+    """Wide items of exactly two key tiles (nothing beyond them to load): many, so that work-groups
+    follow each other on every unit."""
+    g = hq // hkv
+    reqs = [(L, max(0, L - 256 // g)) for L in range(65, 129)] + [(300, 0)]   # (the last: wide tiles at g = 1)
+    print_case(f"two key tiles hq={hq} hkv={hkv} d={d} {len(reqs)} requests")
+    # V scaled by 1/4: a token that attends to a few keys keeps values of up to 5 standard deviations,
+    # whose bf16 rounding (half of 2^-6 from 2 on) with that of the probabilities (2^-9 of them) passes
+    # 1e-2; at a quarter the two are at most 2^-8 + 2^-9 * 1.25 = 6.3e-3
+    b = build_batch(reqs, hq, hkv, d, seed=3300 + g, v_gain=0.25)
+    got, ap = run_attention(b, hq, hkv, d, 256)
+    w = ap.work[: ap.n_work]
+    n = (w[w[:, 0] >= 0, 4] - w[w[:, 0] >= 0, 3] + 63) // 64
+    assert ap.tile_cols == 256 and (n == 2).sum() > 60
+    compare(got, oracle_out(b, hq, hkv, d), "two key tiles")
+
+
 def test_attention_beyond_the_item_key_cap():
     # 70000 keys: every tile's range exceeds one item's 65536-key cap, so the plan splits it and
     # the combine merges the pieces (wide tiles on the ping-pong kernel); sampled rows

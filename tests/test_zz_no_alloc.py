@@ -61,6 +61,19 @@ def test_noalloc_matches_the_workspace_entry_point_call_after_call():
         compare(got, oracle_out(b, hq, hkv, d), f"noalloc case {k}")
 
 
+def test_noalloc_with_work_groups_that_share_units():
+    """head_dim 64 with an odd number of entries (two work-groups per unit), whole and cut tiles."""
+    for k, (reqs, hq, hkv, num_cus, split) in enumerate((([(700, 0), (333, 20)], 8, 8, 32, True),
+                                                         ([(1500, 1000), (700, 100)], 8, 4, 16, False))):
+        print_case(f"noalloc, shared units: {reqs} hq={hq} hkv={hkv} num_cus={num_cus}")
+        b = build_batch(reqs, hq, hkv, 64, seed=780 + k)
+        want, ap = run_attention(b, hq, hkv, 64, num_cus)
+        assert ap.tile_cols == 256 and ap.n_work % 2 == 1 and (ap.n_combine > 0) == split
+        got, _ = run_noalloc(b, hq, hkv, 64, num_cus)
+        assert np.array_equal(got, want)
+        compare(got, oracle_out(b, hq, hkv, 64), "noalloc, shared units")
+
+
 def test_noalloc_refuses_a_plan_larger_than_its_scratch():
     # checked on the host before any launch
     reqs, hq, hkv, d = [(1040, 1024)], 32, 8, 128
