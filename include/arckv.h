@@ -392,7 +392,7 @@ int32_t arckv_prepare_batch_hashed(arckv_cache* cache, const uint64_t* const* ha
  * any bf16 value (16-byte aligned ones are read and written faster).
  * A block-table entry outside [0, num_blocks) is never dereferenced: the kernel reads block 0
  * in its place, so the keys it covers get unspecified (finite or not) values; entries past a
- * request's last block (the -1 padding of a plan's rows) are not read at all.
+ * request's last block (the -1 padding of a plan's rows) are never used.
  * head_dim in {64, 128}; num_q_heads / num_kv_heads in {1, 2, 4, 5, 8}. */
 int32_t arckv_prefill_attention(const void* k_pool, const void* v_pool, const void* q, void* out,
                                 const int32_t* block_tables, int32_t bt_stride,

@@ -49,14 +49,15 @@ constexpr int64_t kItemCost = 4;  // list plans: cost of one item beyond its key
 constexpr int64_t kMinPiece = 4;  // list plans: shortest piece a cut may leave, in key tiles
 constexpr int64_t kXcdSkewPermille = 25;  // work shifted from odd to even XCDs, per mille (measured)
 
-// Uneven wide plans, times in key tiles of a wide tile (1.4 us): what an item costs beside its
-// key tiles (8 us measured); pieces whose partial results are written and read back per key tile
-// (384 pieces, 50 MB: 17 us in the attention kernel, 14 in the combine) and the combine's launch; and
-// the time, in per cent of the equal cut's, up to which the uneven cut is taken (both estimated on
-// the plans as they are dealt).  Measured, equal and uneven cut, with the time estimated for the
-// second in per cent of the first's: 600 tokens
-// on 32768 cached, 64 / 8 heads, 71 %: 745 and 560 us; 4 turns of 300 on 20000, 32 / 8, 74 %: 463 and
-// 378; 8 questions of 128 on 8192, 40 / 8, 95 %: 199 and 197; 5 of 200 on 4000, 100 %: 100 and 102.
+// Uneven wide plans, times in key tiles of a wide tile (1.3 to 1.6 us at head_dim 128, 1.0 at 64):
+// what an item costs beside its key tiles (8 us measured, 5 at head_dim 64); pieces whose partial
+// results are written and read back per key tile (384 pieces, 50 MB: 17 us in the attention kernel,
+// 14 in the combine) and the combine's launch; and the time, in per cent of the equal cut's, up to
+// which the uneven cut is taken (both estimated on the plans as they are dealt).  Measured, equal and
+// uneven cut, with the time estimated for the second in per cent of the first's: 600 tokens on 32768
+// cached, 64 / 8 heads, 71 %: 745 and 560 us (head_dim 64: 498 and 358); 4 turns of 300 on 20000, 32 / 8,
+// 74 %: 463 and 378 (309 and 229); 8 questions of 128 on 8192, 40 / 8, 95 %: 199 and 197; 5 of 200 on
+// 4000, 100 %: 100 and 102.
 constexpr int64_t kWideItemCost = 5;
 constexpr int64_t kSlotsPerKeyTile = 18;
 constexpr int64_t kCombineCost = 2;

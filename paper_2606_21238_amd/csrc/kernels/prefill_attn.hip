@@ -658,7 +658,8 @@ __global__ __launch_bounds__(512, 1) void prefill_attn_list_kernel(
 // ring stage of tile t-4, whose last reader (group 1's M(t-4)) ran in half step 2t-5.  The block
 // numbers come from a copy of the item's block-table slice in LDS, read one tile ahead.
 //
-// Short items are bound by what surrounds the steps (1.6 us each at D = 128): the round trips
+// Short items are bound by what surrounds the steps (1.3 to 1.6 us each at D = 128, by the clock that
+// the load leaves the chip): the round trips
 // before the first MFMA, the output stores, and the next work-group's start.  The prologue asks
 // for everything in two dependent trips and the outputs leave as whole rows: 12 -> 8 us per item,
 // 16 conversation turns (1816 items of 31 steps) 432 -> 419 us.  At D = 64 (80 KiB of LDS, half
@@ -1272,11 +1273,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     store_out<true>(out + (static_cast<int64_t>(q0 + tok) * hq + w.kvh * G + g) * D + 4 * d4, b);   // any alignment
   }
 }
-
-constexpr int kWideNB = 1;  // 32-column MFMA blocks per wave on wide tiles
-constexpr int kWideWaves = arckv::kWideCols / (32 * kWideNB);
-static_assert(kWideWaves * 32 * kWideNB == arckv::kWideCols, "wide tile width");
-
 
 }  // namespace
 

@@ -229,6 +229,7 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
   constexpr int TM = 64 * MB;
   constexpr int XB = TM * kKC * 2, WB = kTN * kKC * 2;  // bytes of an x and of a W stage
   constexpr int XL = TM / 32, WL = kTN / 32;            // 1 KiB loads per wave of each (8 rows)
+  static_assert(XL <= 2 * MB, "every x load has its place in step 0");
   constexpr int kPitch = kTN * 2 + 16;
   constexpr int WS = MB == 2 ? 3 : 2;                   // stages of the W ring
   constexpr int kRing = 3 * XB + WS * WB, kEnd = TM * kPitch + TM * 4;
@@ -339,7 +340,6 @@ __global__ __launch_bounds__(256, 1) void qkv_gemm_rope_kernel(
     auto no_load = [](int) {};
     step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 1, i); },
          [&](int i) __attribute__((always_inline)) { if (i < XL) issue_x(s + 2, x3 == 0 ? 2 : x3 - 1, i); });
-    if constexpr (XL > 2 * MB) static_assert(XL <= 2 * MB, "every x load has its place in the step");
     step(1, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 2, i); }, no_load);
     step(0, [&](int i) __attribute__((always_inline)) { return rd(xo, wo, 3, i); }, no_load);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(XL + (WS - 2) * WL) : "memory");
@@ -424,9 +424,9 @@ __global__ __launch_bounds__(64 * WV, 2) void qkv_ksplit_kernel(
     const int32_t* __restrict__ slots, int64_t n_slots) {
   constexpr int TM = 32 * MB, TN = 32 * NB, ROWS = TM + TN, KC = kKC;
   constexpr int STAGE = ROWS * KC * 2;               // bytes of one wave's stage: x rows, then W rows
-  constexpr int LOADS = STAGE / 1024;                 // 16-byte direct loads per thread per stage (16 rows each)
+  constexpr int LOADS = STAGE / 1024;                 // 16-byte direct loads per thread per stage (8 rows each)
   constexpr int kThr = 64 * WV, NS = WV / 2;          // NS: partial sums held in LDS at the end
-    constexpr int PP = TN + 4;                          // row pitch of the partial sums (floats)
+  constexpr int PP = TN + 4;                          // row pitch of the partial sums (floats)
   constexpr int YP = TN * 2 + 16;                     // row pitch of the y tile (bytes)
   constexpr int YOFS = NS * TM * PP * 4;              // after the loop: partial sums, y tile, (cos, sin)
   constexpr int COFS = YOFS + TM * YP;
@@ -606,11 +606,15 @@ namespace {
 //   T <= 32   eight waves per 32 x 32 tile when every tile has its own compute unit: 11.0 at T =
 //             32 (four waves, two tiles per unit: 11.9; before: 69); else four waves: hidden
 //             8192, 320 tiles: 44.7 against 46.1
-//   T <= 64   four waves, 32 x 32: 14.9 at T = 64 (64 x 32: 15.8; before: 73)
+//   T <= 64   four waves, 32 x 32: 14.9 at T = 64 (64 x 32: 15.8; before: 73).  From T = 33 on two
+//             token tiles read every W row; with W out of the caches, T = 33 and 64: 17.6 and 20.7 (64 x
+//             32: 18.7, 20.3), hidden 1024 6.6 and 7.1 (9.4, 9.7), hidden 5120 23.1 and 28.5 (23.3, 26.0),
+//             hidden 8192 44.4 and 55.4 (47.7, 58.4; 64 x 64: 43.9, 49.9; before: 138, 146)
 //   up to 3.5 64 x 64 tiles per compute unit: 64 x 64 where they fill most of the chip and H is
 //             long enough to outweigh their reduction (T = 256: 30.7, hidden 5120: 38.7 against
 //             46.9 with 64 x 32; before 97 and 137), else 64 x 32 (hidden 1024, 3072 outputs,
-//             T = 256: 10.2 against 13.5).  Past that the prefill kernel's reuse wins: hidden 8192,
+//             T = 256: 10.2 against 13.5; between the two, hidden 2048, 8192 outputs: 29.6 against 23.7
+//             at T = 256, 16.6 and 17.4 at T = 80).  Past that the prefill kernel's reuse wins: hidden 8192,
 //             T = 512 (5 tiles per unit): 112 against 149; hidden 5120, T = 450 (3.5): 78 against 76
 //   prefill   the tile height whose rounds of the chip take least, a round of 128-, 192- and
 //             256-token tiles counted as 3, 4 and 5 (T = 907: 58, 70 and 84 us, one round each).
@@ -620,7 +624,7 @@ namespace {
 //             Not 192 where its last tiles pad the tokens by over 10 % more than 256 does: hidden
 //             8192, T = 1004 (1152 and 1024 tokens, one round each): 157 and 154
 enum class QkvRoute { kK32x32Wide, kK32x32, kK64x32, kK64x64, kG128, kG192, kG256 };
-constexpr int64_t kUnits = 256;   // compute units of an MI355X
+constexpr int64_t kUnits = 256;   // compute units of a whole MI355X (on a part of one another tile may be faster)
 QkvRoute qkv_route(int64_t n_tokens, int64_t hidden, int64_t n_out) {
   auto tiles = [&](int64_t m, int64_t n) { return ((n_tokens + m - 1) / m) * ((n_out + n - 1) / n); };
   if (n_tokens <= 32 && tiles(32, 32) <= kUnits) return QkvRoute::kK32x32Wide;
