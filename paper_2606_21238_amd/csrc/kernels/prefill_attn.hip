@@ -859,7 +859,7 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
   // (group 0 only, 256 threads; published by the barrier that ends the half step)
   auto zero_v_tail = [&](int tile, int t0) {
     uint16_t* vb = reinterpret_cast<uint16_t*>(smem + (tile % kStages) * 2 * TILE + TILE);
-    for (int e = wave * 64 + lane_now(); e < kBK * D; e += kThreads / 2) {
+    for (int e = PAIRED ? wave * 64 + lane_now() : tid; e < kBK * D; e += kThreads / 2) {
       const int key = e & (kBK - 1), d = e / kBK;
       if (t0 + key >= L) {
         const int blk = key >> 4, kk = key & 15;
@@ -1064,8 +1064,9 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
     // Where the loop lies in memory matters at D = 128: with its first P.V MFMA at 16 modulo 32 bytes
     // a step takes 5 to 10 % longer than at any other multiple of 4 (measured in every group size by
     // moving the code 4 bytes at a time: 4 prompts of 1024 on 16384, 16 / 16 heads, 559 us there, 514 to
-    // 520 elsewhere).  From here on the code is the same in every build, so this fixes it (at 4).
-    asm volatile(".p2align 5");
+    // 520 elsewhere; at D = 64 nothing beyond 1.5 % either way).  From here on the code is the same in
+    // every build, so this fixes it (at 4).
+    if constexpr (D == 128) asm volatile(".p2align 5");
     for (; j < n_plain; ++j) step(j, std::false_type{});
     for (; j < ntiles; ++j) step(j, std::true_type{});
     // no load may still write this workgroup's LDS when it ends
@@ -1078,8 +1079,8 @@ __global__ __launch_bounds__(512, PAIRED ? 4 : 1) void prefill_attn_pp_kernel(
   const float lse = lt > 0.f ? m_run + __log2f(lt) : -INFINITY;
 #pragma unroll
   for (int md = 0; md < DM; ++md) o[md] *= inv;
-  // the lane's column once more: PAIRED has no registers to hold it through the loops
-  const int le = lane_now(), r32 = le & 31, he = le >> 5;
+  // the lane's column: PAIRED has no registers to hold it through the loops
+  const int le = PAIRED ? lane_now() : lane, r32 = le & 31, he = le >> 5;
   const int ce = w.col_start + wave * 32 + r32;
   const bool ve = ce < ncols && (q0 + ce / G) < n_q;
   if (w.slot < 0 && ncols - w.col_start <= kCols / 2) {
