@@ -66,12 +66,13 @@ constexpr int64_t kWideGainPercent = 90;
 // head_dim 64: an item beside another on its unit takes up to 1.7 times as long, and the pair less
 // than the two in turn.  That shortens a launch of several rounds and lengthens one that its longest
 // items fill: shared where the longest takes at most this much, in per cent, of the attention
-// kernel's estimated time.  Measured alone and shared, the longest item's part first: 12 prompts of
-// 1100 tokens, 16 / 16 heads, 34 %: 74 and 62 us; 17008 and 9344 cached, 527 and 753 new, 32 / 4,
-// 58 %: 261 and 229; 5 ragged turns, 64 / 8, 69 %: 234 and 225; one prompt of 1339 on 1248, 64 / 8,
-// 74 %: 60.7 and 60.8; 16 ragged turns, one on 60816, 40 / 8, 81 %: 632 and 681; 5 ragged turns, 16 / 8,
-// 256 items in 263 entries, 100 %: 237 and 294; an uneven cut, 600 on 30000, 64 / 8, 100 %: 337 and 397.
-constexpr int64_t kSharePercent = 70;
+// kernel's estimated time.  Shared against alone in 150 drawn batches: 0.83 to 1.02 of the time up to
+// 78 %, 1.00 to 1.10 from 79 to 89 % and 1.02 to 1.21 at 100 %.  Alone and shared, the longest item's
+// part first: 12 prompts of 1100 tokens, 16 / 16 heads, 34 %: 74 and 62 us; 17008 and 9344 cached, 527
+// and 753 new, 32 / 4, 58 %: 261 and 229; 2 turns of 2164 on 3920, 16 / 16, 73 %: 136 and 122; 12 ragged
+// turns, 8 / 8, 84 %: 195 and 214; 5 ragged turns, 16 / 8, 256 items in 263 entries, 100 %: 237 and 294;
+// an uneven cut, 600 on 30000, 64 / 8, 100 %: 337 and 397.
+constexpr int64_t kSharePercent = 78;
 
 // pieces of a tile of nt key tiles cut into pieces of F and a remainder; a remainder under
 // kMinPiece joins the piece before it

@@ -493,6 +493,7 @@ def test_uneven_cut_is_never_the_longer_one():
     ([17008, 9344], [527, 753], 32, 4, 256, True),                 # two XCDs' worth more than units
     ([2000] * 5, [500] * 5, 4, 2, 256, True),                      # two groups on some XCDs, one on others
     ([0] * 2, [1100] * 2, 16, 16, 32, True),
+    ([3920] * 2, [2164] * 2, 16, 16, 256, True),                   # the longest item 73 % of the launch
     ([2000] * 3, [300] * 3, 16, 16, 256, False),                   # fewer items than units
     ([1712, 784, 16304, 6720, 3000], [530, 1707, 684, 75, 300], 16, 8, 256, False),  # 256 items and idle entries
     ([20000] * 4, [300] * 4, 32, 8, 256, False),                   # an uneven cut: one long piece per unit
@@ -507,7 +508,7 @@ def test_paired_work_groups_by_the_longest_item(P, S, hq, hkv, cus, shared):
     w = ap.work[: ap.n_work]
     n = np.where(w[:, 0] >= 0, (w[:, 4] - w[:, 3] + 63) // 64, 0)
     t = finish_key_tiles([[x for x in n[k::8] if x] for k in range(8)], 0, cus)
-    assert (n.max() + 5 <= 0.7 * t) == shared
+    assert (n.max() + 5 <= 0.78 * t) == shared
     ap128 = ak.attention_plan(cu, L, hq, hkv, 128, cus)
     assert ap128.work[ap128.n_work - 1, 0] >= 0
     if w[-1, 0] < 0:
