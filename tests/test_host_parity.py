@@ -517,6 +517,14 @@ def test_paired_work_groups_by_the_longest_item(P, S, hq, hkv, cus, shared):
         ap.work[ap.n_work:], ap128.work[ap128.n_work:])
 
 
+@pytest.mark.parametrize("S,hq,hkv", [(664, 32, 8), (563, 32, 4), (281, 8, 8)])
+def test_short_prompts_are_not_cut(S, hq, hkv):
+    """A tile of up to 11 key tiles is one item where cutting it saves less than its combine."""
+    for d in (64, 128):
+        ap = ak.attention_plan(np.array([0, S], np.int32), [S], hq, hkv, d, 256)
+        assert ap.tile_cols == 256 and ap.n_combine == 0 and ap.ws_bytes == 0
+
+
 def test_list_plans_cover_and_balance():
     """Narrow batches (at most 128 columns per request): per-work-group lists of 8 entries,
     about equal cost per list, no cut piece under 4 key tiles."""
