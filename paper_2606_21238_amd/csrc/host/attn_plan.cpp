@@ -361,7 +361,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
   // and 5 remainders for its 8 units, and the launch took 281 us where an even spread gives 200).
   auto finish_time = [&](const Cut& c, bool with_combine) -> int64_t {
     const int64_t engines = target % (kXcds * kEngines) == 0 ? kEngines : 1;
-    std::vector<int64_t> unit(static_cast<size_t>(target / (kXcds * engines)));
+    std::vector<int64_t> unit(static_cast<size_t>(std::max<int64_t>(1, target / (kXcds * engines))));
     int64_t last = 0;
     for (const auto& v : c.per_xcd)
       for (int64_t e = 0; e < engines; ++e) {

@@ -517,6 +517,13 @@ def test_paired_work_groups_by_the_longest_item(P, S, hq, hkv, cus, shared):
         ap.work[ap.n_work:], ap128.work[ap128.n_work:])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("cus", [1, 2, 7, 8, 9, 31, 304])
+def test_attention_plan_of_any_number_of_units(cus, d):
+    """Fewer units than XCDs, odd numbers of them, more than a whole device has."""
+    attention_plan_coverage([0, 700, 700, 1000], [900, 64, 4000], 8, 4, d, cus)
+
+
 @pytest.mark.parametrize("S,hq,hkv", [(664, 32, 8), (563, 32, 4), (281, 8, 8)])
 def test_short_prompts_are_not_cut(S, hq, hkv):
     """A tile of up to 11 key tiles is one item where cutting it saves less than its combine."""
