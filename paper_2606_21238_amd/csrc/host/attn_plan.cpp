@@ -63,6 +63,7 @@ constexpr int64_t kSlotsPerKeyTile = 18;
 constexpr int64_t kCombineCost = 2;
 constexpr int64_t kWideGainPercent = 90;
 constexpr int64_t kWideFewerPercent = 97;
+constexpr int64_t kMostUnits = 1024;  // no device has more: a caller that names more wants every tile cut that can be
 
 // head_dim 64: an item beside another on its unit takes up to 1.7 times as long, and the pair less
 // than the two in turn.  That shortens a launch of several rounds and lengthens one that its longest
@@ -418,7 +419,7 @@ extern "C" int32_t arckv_attention_plan(const int32_t* cu_q, const int32_t* seq_
     // A cut with fewer partial results than the equal one (short prompts: a remainder under 4 key
     // tiles joins its piece, often leaving nothing cut and no combine) saves what is estimated best:
     // one prompt of 664 tokens, 32 / 8 heads of 64, 94 %: 17.4 us, uneven 15.8.
-    const int64_t gain = slots < plan.slots ? kWideFewerPercent : kWideGainPercent;
+    const int64_t gain = slots < plan.slots && target <= kMostUnits ? kWideFewerPercent : kWideGainPercent;
     // (a piece of F key tiles alone takes this long: most cuts that gain nothing end here, undealt)
     if (lo + kMinPiece <= arckv::kMaxItemKeys / kKeyTile && fits(lo) && slots * slot_bytes <= ARCKV_NOALLOC_MAX_WS_BYTES &&
         (lo + kWideItemCost + (slots > 0 ? slots / kSlotsPerKeyTile + kCombineCost : 0)) * 100 <= before * gain) {
